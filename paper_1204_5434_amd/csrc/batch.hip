@@ -24,6 +24,8 @@ struct BatchGroup {
     int sp_axis[3] = {0, 0, 0};
     int var[3] = {0, 0, 0};      // kernel variants (x, y, z) of the group's grid
     bool fused = false;          // fused yz-plane schedule: zd holds PArgs, sd the x passes only
+    bool mplane = false;         // ... on the matrix cores: zd holds MArgs
+    bool mx = false;             // ... and the x pass beside it: sd holds MXArgs
     hipStream_t s = nullptr;
     hipEvent_t done = nullptr;
     void* zd = nullptr;          // [dir 2][pos maxK+1][R] ZArgs (PArgs when fused)
@@ -98,15 +100,56 @@ void batch_free(pft_batch* b)
     for (pft_ctx* c : b->ctx) pft_destroy(c);
 }
 
+// Argument tables of one group's passes for both sweeps and every sweep
+// position, laid out [position][sweep][replica], where they run on the matrix
+// cores.
+template <typename T>
+pft_status batch_build_m_tables(pft_batch* b, BatchGroup& g)
+{
+    const int R = (int)g.reps.size(), D = g.ndir;
+    std::vector<pft::MArgs<T>> zd((size_t)D * (g.maxK + 1) * R);
+    std::vector<pft::MXArgs<T>> xd(g.mx ? (size_t)D * g.maxK * R : 0);
+    for (int dir = 0; dir < D; ++dir)
+        for (int ri = 0; ri < R; ++ri) {
+            pft_ctx* c = b->ctx[g.reps[ri]];
+            const int K = c->K;
+            auto stepj = [&](int i) { return dir ? K - 1 - i : i; };
+            void* store = dir ? c->qds : c->qs;
+            const Work w{dir ? c->U2 : c->U, dir ? c->V2 : c->V, nullptr};
+            for (int p = 0; p <= g.maxK; ++p) {
+                const size_t at = ((size_t)p * D + dir) * R + ri;
+                if (p > K)
+                    zd[at].skip = 1;
+                else
+                    zd[at] = margs<T>(c, p > 0 ? stepj(p - 1) : -1, p < K ? stepj(p) : -1, nullptr, slice<T>(store, c, p), w);
+                if (!g.mx || p >= g.maxK) continue;
+                if (p >= K)
+                    xd[at].skip = 1;
+                else
+                    xd[at] = mxargs<T>(c, stepj(p), w);
+            }
+        }
+    PFT_BHIP(b, hipMalloc(&g.zd, zd.size() * sizeof(zd[0])));
+    PFT_BHIP(b, hipMemcpy(g.zd, zd.data(), zd.size() * sizeof(zd[0]), hipMemcpyHostToDevice));
+    if (!g.mx) return PFT_OK;
+    PFT_BHIP(b, hipMalloc(&g.sd, xd.size() * sizeof(xd[0])));
+    PFT_BHIP(b, hipMemcpy(g.sd, xd.data(), xd.size() * sizeof(xd[0]), hipMemcpyHostToDevice));
+    return PFT_OK;
+}
+
 // Argument tables of the passes of one group, for both sweeps and every
 // sweep position; a replica whose K is exhausted is marked skip.
 template <typename T>
 pft_status batch_build_pass_tables(pft_batch* b, BatchGroup& g)
 {
+    if (g.mplane) {
+        const pft_status s = batch_build_m_tables<T>(b, g);
+        if (s || g.mx) return s;
+    }
     const int R = (int)g.reps.size();
     const int D = g.ndir;
     std::vector<pft::ZArgs<T>> zd(g.fused ? 0 : (size_t)D * (g.maxK + 1) * R);
-    std::vector<pft::PArgs<T>> pd(g.fused ? (size_t)D * (g.maxK + 1) * R : 0);
+    std::vector<pft::PArgs<T>> pd(g.fused && !g.mplane ? (size_t)D * (g.maxK + 1) * R : 0);
     std::vector<pft::SArgs<T>> sd((size_t)D * g.maxK * g.npass * R);
     for (int dir = 0; dir < g.ndir; ++dir)
         for (int ri = 0; ri < R; ++ri) {
@@ -121,7 +164,9 @@ pft_status batch_build_pass_tables(pft_batch* b, BatchGroup& g)
                 const int i = p - 1;  // Z (or yz) at position p completes step i and starts step i + 1
                 const size_t at = ((size_t)p * D + dir) * R + ri;
                 const int prev = i >= 0 ? stepj(i) : -1, next = i + 1 < K ? stepj(i + 1) : -1;
-                if (g.fused) {
+                if (g.mplane) {
+                    continue;
+                } else if (g.fused) {
                     if (i >= K) {
                         pd[at].skip = 1;
                     } else {
@@ -158,11 +203,13 @@ pft_status batch_build_pass_tables(pft_batch* b, BatchGroup& g)
                 }
             }
         }
-    const size_t zbytes = g.fused ? pd.size() * sizeof(pd[0]) : zd.size() * sizeof(zd[0]);
-    PFT_BHIP(b, hipMalloc(&g.zd, zbytes));
+    if (!g.mplane) {
+        const size_t zbytes = g.fused ? pd.size() * sizeof(pd[0]) : zd.size() * sizeof(zd[0]);
+        PFT_BHIP(b, hipMalloc(&g.zd, zbytes));
+        PFT_BHIP(b, hipMemcpy(g.zd, g.fused ? (const void*)pd.data() : (const void*)zd.data(), zbytes,
+                              hipMemcpyHostToDevice));
+    }
     PFT_BHIP(b, hipMalloc(&g.sd, std::max<size_t>(1, sd.size()) * sizeof(pft::SArgs<T>)));
-    PFT_BHIP(b, hipMemcpy(g.zd, g.fused ? (const void*)pd.data() : (const void*)zd.data(), zbytes,
-                          hipMemcpyHostToDevice));
     if (!sd.empty()) PFT_BHIP(b, hipMemcpy(g.sd, sd.data(), sd.size() * sizeof(sd[0]), hipMemcpyHostToDevice));
     return PFT_OK;
 }
@@ -308,13 +355,17 @@ pft_status batch_enqueue_group(pft_batch* b, BatchGroup& g, int slot, bool updat
     // the z pass, or the fused yz pass, at sweep position p
     auto zlaunch = [&](int p) -> hipError_t {
         const size_t at = (size_t)p * DR;
+        if (g.mplane) return pft::launch_myz_batch<T>(g.ny, g.nx, static_cast<const pft::MArgs<T>*>(g.zd) + at, DR, s);
         if (g.fused) return pft::launch_yzpass_batch<T>(g.ny, g.nx, pd + at, DR, s);
         if (g.bc[2]) return pft::launch_zpass_walls_batch<T>(g.nz, g.bc[2], nlines, zd + at, DR, s);
         return pft::launch_zpass_batch<T>(g.nz, g.var[2], nlines, zd + at, DR, s);
     };
     PFT_BHIP(b, zlaunch(0));
     for (int p = 0; p < g.maxK; ++p) {
-        for (int k = 0; k < g.npass; ++k) {
+        if (g.mx)
+            PFT_BHIP(b, pft::launch_mx_batch<T>(g.nx, g.ny * g.nz,
+                                                static_cast<const pft::MXArgs<T>*>(g.sd) + (size_t)p * DR, DR, s));
+        for (int k = 0; k < g.npass && !g.mx; ++k) {
             const int ax = g.sp_axis[k];
             const pft::SArgs<T>* at = sd + ((size_t)p * g.npass + k) * DR;
             if (g.bc[ax])
@@ -554,6 +605,8 @@ pft_status pft_batch_create(const pft_params* params, int32_t n, void* hip_strea
             for (int a = 0; a < 3; ++a) g->bc[a] = p.bc[a];
             g->ndir = p.model == PFT_EDWARDS ? 1 : 2;
             g->fused = fused;
+            g->mplane = fused && b->ctx[r]->mplane;
+            g->mx = g->mplane && b->ctx[r]->mx;
             if (g->fused) {
                 g->npass = 1;  // the x pass; the y and z work runs in the yz pass
                 g->sp_axis[0] = 0;

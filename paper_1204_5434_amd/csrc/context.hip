@@ -140,6 +140,10 @@ pft_status propagate_t(pft_ctx* c, const double* wp, const double* wm)
         // symmetric chain: q-dagger = q, one sweep
         s = sweep<T>(c, false, c->qs);
         if (s) return s;
+    } else if (c->together && c->fused && !c->fused_conj_only && c->mx && c->s2 && !c->dual_off) {
+        // small grids: launches and latency count, so both sweeps share each launch
+        s = sweeps_together<T>(c);
+        if (s) return s;
     } else if (c->s2 && !c->dual_off) {
         // the two sweeps are independent: the conjugate one runs on a second
         // stream with its own work pair, so one sweep's memory phases overlap
@@ -237,7 +241,7 @@ void free_all(pft_ctx* c)
     c->qh = nullptr;
     void* bufs[] = {c->qs,  c->qds,  c->U,        c->V,    c->U2,    c->V2,  c->E,   c->work,
                     c->gtab, c->tau, c->phi,      c->partials, c->scal, c->flags, c->adj, c->adjG,
-                    c->adjAcc, c->k2, c->sisbuf, c->sisext, c->ring};
+                    c->adjAcc, c->k2, c->sisbuf, c->sisext, c->ring, c->mtab};
     for (void* b : bufs)
         if (b) (void)hipFree(b);
 }
@@ -371,8 +375,10 @@ std::vector<T> wall_factors(int n, double L, double h, int bc, bool lap = false)
     return ab;
 }
 
+// Factors of a step of length h (half and full, all axes) in slot `hid` of a
+// host copy of the table.
 template <typename T>
-pft_status upload_factors(pft_ctx* c, int hid, double h)
+void step_factors(const pft_ctx* c, int hid, double h, T* tab)
 {
     const int n[3] = {c->p.nx, c->p.ny, c->p.nz};
     const double L[3] = {c->p.lx, c->p.ly, c->p.lz};
@@ -381,35 +387,65 @@ pft_status upload_factors(pft_ctx* c, int hid, double h)
             const double hh = full ? h : h / 2;
             const std::vector<T> g = c->p.bc[ax] ? wall_factors<T>(n[ax], L[ax], hh, c->p.bc[ax])
                                                  : axis_factors<T>(n[ax], L[ax], hh);
-            PFT_HIP(c, hipMemcpy(const_cast<T*>(gptr<T>(c, hid, full, ax)), g.data(), g.size() * sizeof(T),
-                                 hipMemcpyHostToDevice));
+            std::copy(g.begin(), g.end(), tab + (size_t)((hid * 2 + full) * 3 + ax) * c->maxN);
         }
-    return PFT_OK;
 }
 
-// Spectral -d^2/dx_a^2 per axis, (2 pi m / L_a)^2 / N_a, in table slot 4
-// (walled axes: the pair factors of (pi m / L_a)^2 / N_a).
+// The step tables of the context (slots 0-2) and the spectral -d^2/dx_a^2 per
+// axis, (2 pi m / L_a)^2 / N_a, in slot 4 (walled axes: the pair factors of
+// (pi m / L_a)^2 / N_a), in one copy.
 template <typename T>
-pft_status upload_second_derivative(pft_ctx* c)
+pft_status upload_tables(pft_ctx* c)
 {
     const int n[3] = {c->p.nx, c->p.ny, c->p.nz};
     const double L[3] = {c->p.lx, c->p.ly, c->p.lz};
+    std::vector<T> tab((size_t)5 * 2 * 3 * c->maxN, T(0));
+    for (int hd = 0; hd < 3; ++hd) step_factors<T>(c, hd, c->hval[hd] > 0 ? c->hval[hd] : c->hval[0], tab.data());
     for (int ax = 0; ax < 3; ++ax) {
+        T* out = tab.data() + (size_t)(4 * 2 * 3 + ax) * c->maxN;
         if (c->p.bc[ax]) {
             const std::vector<T> g = wall_factors<T>(n[ax], L[ax], 0.0, c->p.bc[ax], true);
-            PFT_HIP(c, hipMemcpy(const_cast<T*>(gptr<T>(c, 4, 0, ax)), g.data(), g.size() * sizeof(T),
-                                 hipMemcpyHostToDevice));
+            std::copy(g.begin(), g.end(), out);
             continue;
         }
-        std::vector<T> g(n[ax]);
         for (int j = 0; j < n[ax]; ++j) {
             const int m = (j <= n[ax] / 2) ? j : j - n[ax];
             const double k = kTwoPi * m / L[ax];
-            g[j] = T(k * k / n[ax]);
+            out[j] = T(k * k / n[ax]);
         }
-        PFT_HIP(c, hipMemcpy(const_cast<T*>(gptr<T>(c, 4, 0, ax)), g.data(), g.size() * sizeof(T),
-                             hipMemcpyHostToDevice));
     }
+    PFT_HIP(c, hipMemcpy(c->gtab, tab.data(), tab.size() * sizeof(T), hipMemcpyHostToDevice));
+    return PFT_OK;
+}
+
+// Matrices of the matrix-core passes for every step length of the contour.
+template <typename T>
+pft_status upload_matrices(pft_ctx* c)
+{
+    if (!c->mtab) return PFT_OK;
+    const int n[3] = {c->p.nx, c->p.ny, c->p.nz};
+    const double L[3] = {c->p.lx, c->p.ly, c->p.lz};
+    std::vector<T> tab(6 * c->moff[3], T(0));
+    for (int hd = 0; hd < 3; ++hd) {
+        if (hd > 0 && !(c->hval[hd] > 0)) continue;  // no junction sub-steps
+        for (int full = 0; full < 2; ++full)
+            for (int ax = 0; ax < 3; ++ax) {
+                if (ax == 0 ? !c->mx : !c->mplane) continue;
+                T* out = tab.data() + (size_t)(hd * 2 + full) * c->moff[3] + c->moff[ax];
+                if (ax == 2 && n[2] == n[1] && L[2] == L[1]) {
+                    std::copy_n(out - (c->moff[2] - c->moff[1]), c->moff[2] - c->moff[1], out);
+                    continue;
+                }
+                std::vector<double> g(n[ax]);
+                for (int j = 0; j < n[ax]; ++j) {
+                    const int m = (j <= n[ax] / 2) ? j : j - n[ax];
+                    const double k = kTwoPi * m / L[ax];
+                    g[j] = std::exp(-k * k * (full ? c->hval[hd] : c->hval[hd] / 2));
+                }
+                pft::mtable<T>(n[ax], g, out);
+            }
+    }
+    PFT_HIP(c, hipMemcpy(c->mtab, tab.data(), tab.size() * sizeof(T), hipMemcpyHostToDevice));
     return PFT_OK;
 }
 
@@ -421,8 +457,11 @@ template <typename T>
 pft_status diffuse_t(pft_ctx* c, double* u, double h)
 {
     PFT_HIP(c, hipStreamSynchronize(c->stream));  // earlier work may still read the spare slot
-    pft_status s = upload_factors<T>(c, 3, h);
-    if (s) return s;
+    std::vector<T> tab((size_t)4 * 2 * 3 * c->maxN, T(0));
+    step_factors<T>(c, 3, h, tab.data());
+    const size_t slot = (size_t)3 * 2 * 3 * c->maxN;
+    PFT_HIP(c, hipMemcpy(static_cast<T*>(c->gtab) + slot, tab.data() + slot, (tab.size() - slot) * sizeof(T),
+                         hipMemcpyHostToDevice));
     cx<T>* w0 = static_cast<cx<T>*>(c->work);
     hipLaunchKernelGGL((k_to_work<T>), dim3(grid_for(c->M, 256)), dim3(256), 0, c->stream,
                        reinterpret_cast<const double2*>(u), w0, c->M);
@@ -438,7 +477,7 @@ pft_status diffuse_t(pft_ctx* c, double* u, double h)
     a.gf_n = gptr<T>(c, 3, 1, 2);
     PFT_HIP(c, launch_z<T>(c, a, c->stream));
     const pft::SOps<T> none{nullptr, nullptr, nullptr};
-    s = spass<T>(c, 1, none, {gptr<T>(c, 3, 1, 1), nullptr, nullptr});
+    pft_status s = spass<T>(c, 1, none, {gptr<T>(c, 3, 1, 1), nullptr, nullptr});
     if (s) return s;
     s = spass<T>(c, 0, none, {gptr<T>(c, 3, 1, 0), nullptr, nullptr});
     if (s) return s;
@@ -463,10 +502,16 @@ constexpr int kFusedMaxSpill = 256;
 // ms), with 248 (absorbing walls on y and z) it loses (12.39 against 11.85).
 constexpr int kFusedMaxSpillWalls = 128;
 
+// Grids up to this many sites run both sweeps in the same launches.
+constexpr int64_t kTogetherMax = 64 * 64 * 64;
+
 // Walls along y or z have a fused pass in complex float only.
 static bool fused_supported(const pft_params& p)
 {
     if (p.ny != p.nz) return false;
+    if (!p.bc[1] && !p.bc[2] &&
+        (p.precision == PFT_C128 ? pft::mplane_supported<double>(p.ny) : pft::mplane_supported<float>(p.ny)))
+        return true;
     if (p.bc[1] || p.bc[2]) return p.precision == PFT_C64 && pft::plane_walls_supported(p.ny);
     return p.precision == PFT_C128 ? pft::plane_supported<double>(p.ny) : pft::plane_supported<float>(p.ny);
 }
@@ -516,7 +561,12 @@ pft_status create_ctx(const pft_params* params, void* hip_stream, bool dual, pft
     c->var[0] = tuned_variant(p.precision, p.nx, 1);
     c->var[1] = tuned_variant(p.precision, p.ny, 2);
     c->var[2] = tuned_variant(p.precision, p.nz, 0);
-    c->fused = fused_default(p);
+    const bool dbl = p.precision == PFT_C128;
+    c->mplane = p.ny == p.nz && !p.bc[1] && !p.bc[2] &&
+                (dbl ? pft::mplane_supported<double>(p.ny) : pft::mplane_supported<float>(p.ny));
+    c->mx = c->mplane && !p.bc[0] && (dbl ? pft::mx_supported<double>(p.nx) : pft::mx_supported<float>(p.nx));
+    c->fused = c->mplane || fused_default(p);
+    c->together = (int64_t)p.nx * p.ny * p.nz <= kTogetherMax;
     c->stream = static_cast<hipStream_t>(hip_stream);
     c->M = (int64_t)p.nx * p.ny * p.nz;
     // table slot length: n factors per periodic axis, 3n per walled axis
@@ -559,6 +609,11 @@ pft_status create_ctx(const pft_params* params, void* hip_stream, bool dual, pft
     }
     c->nparts = reduction_blocks(c->M);
 
+    {
+        const int n[3] = {p.nx, p.ny, p.nz};
+        for (int ax = 0; ax < 3; ++ax)
+            c->moff[ax + 1] = c->moff[ax] + ((ax == 0 ? c->mx : c->mplane) ? pft::MSplitRt(n[ax]).size() : 0);
+    }
     auto alloc = [&](void** ptr, size_t bytes) -> bool { return hipMalloc(ptr, std::max<size_t>(bytes, 16)) == hipSuccess; };
     const size_t store = (size_t)(c->K + 1) * c->M * c->elem;
     const bool both = p.storage == PFT_STORE_BOTH, host = p.storage == PFT_STORE_HOST;
@@ -568,6 +623,7 @@ pft_status create_ctx(const pft_params* params, void* hip_stream, bool dual, pft
               alloc(&c->V, c->M * c->elem) && (!dual || (alloc(&c->U2, c->M * c->elem) && alloc(&c->V2, c->M * c->elem))) &&
               alloc(&c->E, 4 * c->M * c->elem) && alloc(&c->work, 2 * c->M * c->elem) &&
               alloc(&c->gtab, (size_t)5 * 2 * 3 * c->maxN * (c->elem / 2)) &&
+              (!c->moff[3] || alloc(&c->mtab, 6 * c->moff[3] * (c->elem / 2))) &&
               alloc((void**)&c->tau, tau.size() * sizeof(double)) && alloc((void**)&c->phi, 2 * c->M * sizeof(double2)) &&
               alloc((void**)&c->partials, (size_t)std::max(c->nparts, 64 * (c->K + 1)) * sizeof(double2)) &&
               alloc((void**)&c->scal, (size_t)(8 + c->K + 1) * sizeof(double2)) && alloc((void**)&c->flags, sizeof(uint32_t));
@@ -602,11 +658,8 @@ pft_status create_ctx(const pft_params* params, void* hip_stream, bool dual, pft
     if (hipMemcpy(c->tau, tau.data(), tau.size() * sizeof(double), hipMemcpyHostToDevice) != hipSuccess ||
         hipMemset(c->flags, 0, sizeof(uint32_t)) != hipSuccess || hipMemset(c->scal, 0, (8 + c->K + 1) * sizeof(double2)) != hipSuccess)
         s = PFT_E_DEVICE;
-    for (int hd = 0; hd < 3 && s == PFT_OK; ++hd) {
-        const double hv = c->hval[hd] > 0 ? c->hval[hd] : ds;
-        s = p.precision == PFT_C128 ? upload_factors<double>(c, hd, hv) : upload_factors<float>(c, hd, hv);
-    }
-    if (s == PFT_OK) s = p.precision == PFT_C128 ? upload_second_derivative<double>(c) : upload_second_derivative<float>(c);
+    if (s == PFT_OK) s = p.precision == PFT_C128 ? upload_tables<double>(c) : upload_tables<float>(c);
+    if (s == PFT_OK) s = p.precision == PFT_C128 ? upload_matrices<double>(c) : upload_matrices<float>(c);
     if (s != PFT_OK) {
         free_all(c);
         delete c;
@@ -1038,12 +1091,9 @@ pft_status pft_set_box(pft_ctx* c, double lx, double ly, double lz)
     c->p.lz = lz;
     c->propagated = false;
     const bool dbl = c->p.precision == PFT_C128;
-    for (int hd = 0; hd < 3; ++hd) {
-        const double hv = c->hval[hd] > 0 ? c->hval[hd] : c->hval[0];
-        const pft_status s = dbl ? upload_factors<double>(c, hd, hv) : upload_factors<float>(c, hd, hv);
-        if (s) return s;
-    }
-    const pft_status s = dbl ? upload_second_derivative<double>(c) : upload_second_derivative<float>(c);
+    pft_status s = dbl ? upload_tables<double>(c) : upload_tables<float>(c);
+    if (s) return s;
+    s = dbl ? upload_matrices<double>(c) : upload_matrices<float>(c);
     if (s) return s;
     if (c->k2) return sis_upload_k2(c);
     return PFT_OK;

@@ -81,11 +81,6 @@ struct PShape {
     static constexpr int kPWlds = kPlaneBytes >= 65536 ? 1 : int(65536 / kPlaneBytes);
     static constexpr int kPW = kPW0 < kPWlds ? kPW0 : kPWlds;
     static constexpr int kThreads = kPW * kPlaneThreads;
-    // Register bound of the batched kernel (minimum waves per SIMD): the
-    // complex-float 40^2 pass (20 x 2 lines) runs at three waves per SIMD
-    // (168 registers, a 76-byte spill) instead of two (207 registers): the
-    // 256-replica field step 41.6 -> 40.8 ms (both forms timed alternately on one device).
-    static constexpr int kBatchMinWaves = (std::is_same<T, float>::value && N1 == 20 && N2 == 2) ? 3 : 1;
     static constexpr int64_t kLdsBytes = kPW * kPlaneBytes;
 };
 
@@ -297,7 +292,7 @@ __global__ __launch_bounds__((PShape<T, N1, N2>::kThreads)) void k_yzpass(PArgs<
 }
 
 template <typename T, int N1, int N2>
-__global__ __launch_bounds__((PShape<T, N1, N2>::kThreads), (PShape<T, N1, N2>::kBatchMinWaves)) void k_yzpass_batch(
+__global__ __launch_bounds__((PShape<T, N1, N2>::kThreads)) void k_yzpass_batch(
     const PArgs<T>* __restrict__ descs)
 {
     __shared__ __align__(16) unsigned char smem_raw[PShape<T, N1, N2>::kLdsBytes];
@@ -315,32 +310,30 @@ __global__ __launch_bounds__((PShape<T, N1, N2>::kThreads)) void k_yzpass_walls(
 }
 
 // Plane sizes N (= ny = nz) with a fused kernel per precision, as (N, N1, N2):
-// the default axis splits whose padded plane fits in LDS.
+// the default axis splits whose padded plane fits in LDS, from 80 up (smaller
+// planes run on the matrix cores, mplanes.h, which is faster there: 32^3 in
+// complex float 6.0 against 21.4 us, 64^3 in complex double 20.1 against 23.2).
 #define PFT_PLANE_SIZES_F32(X) \
-    X(8, 8, 1)                 \
-    X(12, 12, 1)               \
-    X(16, 16, 1)               \
-    X(20, 20, 1)               \
-    X(24, 12, 2)               \
-    X(32, 16, 2)               \
-    X(40, 20, 2)               \
-    X(48, 12, 4)               \
-    X(64, 16, 4)               \
     X(80, 20, 4)               \
     X(96, 24, 4)               \
     X(128, 16, 8)
 #define PFT_PLANE_SIZES_F64(X) \
-    X(8, 8, 1)                 \
-    X(12, 12, 1)               \
-    X(16, 16, 1)               \
-    X(20, 20, 1)               \
-    X(24, 12, 2)               \
-    X(32, 16, 2)               \
-    X(40, 20, 2)               \
-    X(48, 12, 4)               \
-    X(64, 16, 4)               \
     X(80, 20, 4)               \
     X(96, 24, 4)
+// Between walls (complex float) every size runs here.
+#define PFT_PLANE_SIZES_WALLS(X) \
+    X(8, 8, 1)                   \
+    X(12, 12, 1)                 \
+    X(16, 16, 1)                 \
+    X(20, 20, 1)                 \
+    X(24, 12, 2)                 \
+    X(32, 16, 2)                 \
+    X(40, 20, 2)                 \
+    X(48, 12, 4)                 \
+    X(64, 16, 4)                 \
+    X(80, 20, 4)                 \
+    X(96, 24, 4)                 \
+    X(128, 16, 8)
 
 // True if the fused pass exists for a square yz-plane of side n.
 template <typename T>

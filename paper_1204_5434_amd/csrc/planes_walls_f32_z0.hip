@@ -4,7 +4,14 @@
 
 namespace pft {
 
-bool plane_walls_supported(int n) { return plane_supported<float>(n); }
+bool plane_walls_supported(int n)
+{
+#define PFT_CASE(N, N1, N2) \
+    if (n == N) return true;
+    PFT_PLANE_SIZES_WALLS(PFT_CASE)
+#undef PFT_CASE
+    return false;
+}
 
 int plane_walls_private_bytes(int n, int ey, int ez)
 {

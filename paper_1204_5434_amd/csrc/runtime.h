@@ -17,6 +17,8 @@
 
 #include "../../include/pft.h"
 #include "kernels.h"
+#include "mplanes.h"
+#include "mtable.h"
 #include "ops.h"
 #include "planes.h"
 #include "sis.h"
@@ -50,6 +52,9 @@ struct pft_ctx {
     int var[3] = {0, 0, 0};           // kernel variant of each axis pass (x, y, z)
     bool fused = false;               // sweeps use the fused yz-plane pass (square yz-plane in LDS)
     bool fused_conj_only = false;     // ... only the conjugate sweep (the forward one runs axis passes)
+    bool mplane = false;              // the fused pass runs on the matrix cores
+    bool mx = false;                  // ... and so does the x pass beside it
+    bool together = false;            // both sweeps advance in the same launches (small grids)
     size_t elem = 0;                  // bytes per propagator value
     // device buffers
     void* qs = nullptr;
@@ -64,6 +69,8 @@ struct pft_ctx {
     void* E = nullptr;     // 4 * M field operator tables
     void* work = nullptr;  // 2 * M scratch in working precision
     void* gtab = nullptr;  // diffusion factors: [hid 3][half/full 2][axis 3][maxN]
+    void* mtab = nullptr;  // matrices of the matrix-core passes: [hid 3][half/full 2][x, y, z]
+    size_t moff[4] = {0, 0, 0, 0};  // ... offsets of the axes within one set, and the set's size
     double* tau = nullptr; // 2 (K+1) trapezoid weights
     double2* phi = nullptr;       // internal phi_A, phi_B (2 M)
     double* k2 = nullptr;         // semi-implicit step: (2 pi m / L)^2 per axis [3][maxN], natural order
@@ -184,6 +191,13 @@ const T* gptr(const pft_ctx* c, int hid, int full, int axis)
     return static_cast<const T*>(c->gtab) + ((size_t)((hid * 2 + full) * 3 + axis)) * c->maxN;
 }
 
+// Matrix table of one axis (matrix-core passes).
+template <typename T>
+const T* mptr(const pft_ctx* c, int hid, int full, int axis)
+{
+    return static_cast<const T*>(c->mtab) + (size_t)(hid * 2 + full) * c->moff[3] + c->moff[axis];
+}
+
 template <typename T>
 cx<T>* etab(const pft_ctx* c, int kind)
 {
@@ -287,17 +301,13 @@ pft_status spass(pft_ctx* c, int axis, pft::SOps<T> opU, pft::SOps<T> opV, const
     return PFT_OK;
 }
 
-// Fused yz-plane pass completing step `prev` (-1: none: its Y2 and Z) and
-// starting step `next` (-1: none: its Z and Y1).
 template <typename T>
-pft_status yzpass(pft_ctx* c, int prev, int next, const cx<T>* qin, cx<T>* qout, const Work& w = Work(),
-                  cx<T>* hcap = nullptr)
+pft::PArgs<T> pargs(const pft_ctx* c, int prev, int next, const cx<T>* qin, cx<T>* qout)
 {
     pft::PArgs<T> a{};
     a.nplanes = c->p.nx;
-    a.U = static_cast<cx<T>*>(w.U ? w.U : c->U);
-    a.V = static_cast<cx<T>*>(w.V ? w.V : c->V);
-    a.hcap = hcap;
+    a.U = static_cast<cx<T>*>(c->U);
+    a.V = static_cast<cx<T>*>(c->V);
     a.qin = qin;
     a.qout = qout;
     a.scheme = c->p.scheme;
@@ -315,7 +325,12 @@ pft_status yzpass(pft_ctx* c, int prev, int next, const cx<T>* qin, cx<T>* qout,
         a.gyh_n = gptr<T>(c, c->hid[next], 0, 1);
         a.gyf_n = gptr<T>(c, c->hid[next], 1, 1);
     }
-    // algorithmic bytes, as for the z pass
+    return a;
+}
+
+// Algorithmic bytes of a z or yz pass: each distinct array read or written once.
+inline double zbytes(const pft_ctx* c, int prev, int next, bool qin, bool qout, bool hcap)
+{
     const double E = (double)c->elem * (double)c->M;
     const bool rqm4 = c->p.scheme == PFT_RQM4;
     double bytes = 0;
@@ -324,8 +339,72 @@ pft_status yzpass(pft_ctx* c, int prev, int next, const cx<T>* qin, cx<T>* qout,
     if (qout) bytes += E;
     if (next >= 0) bytes += (rqm4 ? 2 : 1) * E + ((prev < 0 || c->kind[next] != c->kind[prev]) ? E : 0);
     if (hcap) bytes += E;
+    return bytes;
+}
+
+// Argument sets of the matrix-core passes.
+template <typename T>
+pft::MArgs<T> margs(const pft_ctx* c, int prev, int next, const cx<T>* qin, cx<T>* qout, const Work& w = Work(),
+                    cx<T>* hcap = nullptr)
+{
+    pft::MArgs<T> a{};
+    a.nplanes = c->p.nx;
+    a.U = static_cast<cx<T>*>(w.U ? w.U : c->U);
+    a.V = static_cast<cx<T>*>(w.V ? w.V : c->V);
+    a.hcap = hcap;
+    a.qin = qin;
+    a.qout = qout;
+    a.scheme = c->p.scheme;
+    a.has_prev = prev >= 0;
+    a.has_next = next >= 0;
+    if (prev >= 0) {
+        a.Ep = etab<T>(c, c->kind[prev]);
+        a.fyh_p = mptr<T>(c, c->hid[prev], 0, 1);
+        a.fzh_p = mptr<T>(c, c->hid[prev], 0, 2);
+    }
+    if (next >= 0) {
+        a.En = etab<T>(c, c->kind[next]);
+        a.fzh_n = mptr<T>(c, c->hid[next], 0, 2);
+        a.fzf_n = mptr<T>(c, c->hid[next], 1, 2);
+        a.fyh_n = mptr<T>(c, c->hid[next], 0, 1);
+        a.fyf_n = mptr<T>(c, c->hid[next], 1, 1);
+    }
+    return a;
+}
+
+template <typename T>
+pft::MXArgs<T> mxargs(const pft_ctx* c, int j, const Work& w = Work(), cx<T>* capA = nullptr, cx<T>* capC = nullptr)
+{
+    const bool rqm4 = c->p.scheme == PFT_RQM4;
+    pft::MXArgs<T> a{};
+    a.ncols = c->p.ny * c->p.nz;
+    a.U = rqm4 ? static_cast<cx<T>*>(w.U ? w.U : c->U) : nullptr;
+    a.V = static_cast<cx<T>*>(w.V ? w.V : c->V);
+    a.E = rqm4 ? etab<T>(c, c->kind[j]) : nullptr;
+    a.fh = mptr<T>(c, c->hid[j], 0, 0);
+    a.ff = mptr<T>(c, c->hid[j], 1, 0);
+    a.capU = rqm4 ? capA : nullptr;
+    a.capV = rqm4 ? capC : nullptr;
+    return a;
+}
+
+// Fused yz-plane pass completing step `prev` (-1: none: its Y2 and Z) and
+// starting step `next` (-1: none: its Z and Y1).
+template <typename T>
+pft_status yzpass(pft_ctx* c, int prev, int next, const cx<T>* qin, cx<T>* qout, const Work& w = Work(),
+                  cx<T>* hcap = nullptr)
+{
     hipStream_t st = w.stream ? w.stream : c->stream;
-    ProfScope ps(c, PFT_K_YZPASS, bytes, st, true);
+    ProfScope ps(c, PFT_K_YZPASS, zbytes(c, prev, next, qin, qout, hcap), st, true);
+    if (c->mplane) {
+        const pft::MArgs<T> m = margs<T>(c, prev, next, qin, qout, w, hcap);
+        PFT_HIP(c, pft::launch_myz<T>(c->p.ny, m, m, 1, st));
+        return PFT_OK;
+    }
+    pft::PArgs<T> a = pargs<T>(c, prev, next, qin, qout);
+    if (w.U) a.U = static_cast<cx<T>*>(w.U);
+    if (w.V) a.V = static_cast<cx<T>*>(w.V);
+    a.hcap = hcap;
     if (c->p.bc[1] || c->p.bc[2]) {
         if constexpr (std::is_same<T, float>::value)
             PFT_HIP(c, pft::launch_yzpass_walls(c->p.ny, c->p.bc[1], c->p.bc[2], a, st));
@@ -337,12 +416,26 @@ pft_status yzpass(pft_ctx* c, int prev, int next, const cx<T>* qin, cx<T>* qout,
     return PFT_OK;
 }
 
+// Algorithmic bytes of an x pass.
+inline double xbytes(const pft_ctx* c, bool capA, bool capC)
+{
+    const double E = (double)c->elem * (double)c->M;
+    return (c->p.scheme == PFT_RQM4 ? 5 + capA + capC : 2) * E;
+}
+
 // The x pass of step j alone (the fused schedule's other pass).
 template <typename T>
 pft_status xpass_step(pft_ctx* c, int j, const Work& w = Work(), cx<T>* capA = nullptr, cx<T>* capC = nullptr)
 {
     const int hd = c->hid[j];
     const cx<T>* e = etab<T>(c, c->kind[j]);
+    if (c->mx) {
+        hipStream_t st = w.stream ? w.stream : c->stream;
+        const pft::MXArgs<T> m = mxargs<T>(c, j, w, capA, capC);
+        ProfScope ps(c, PFT_K_XPASS, xbytes(c, capA, capC), st, true);
+        PFT_HIP(c, pft::launch_mx<T>(c->p.nx, m, m, 1, st));
+        return PFT_OK;
+    }
     if (c->p.scheme == PFT_RQM4)
         return spass<T>(c, 0, {gptr<T>(c, hd, 0, 0), e, gptr<T>(c, hd, 0, 0), capA},
                         {gptr<T>(c, hd, 1, 0), e, nullptr, capC}, w);
@@ -410,6 +503,33 @@ pft_status sweep(pft_ctx* c, bool backward, void* store, const Work& w = Work())
                           [](int) { return PFT_OK; });
 }
 
+// Both sweeps in the same launches, each on its own work pair.
+template <typename T>
+pft_status sweeps_together(pft_ctx* c)
+{
+    const int K = c->K;
+    const Work wb{c->U2, c->V2, nullptr};
+    auto yz = [&](int i) -> pft_status {  // completes step i - 1 of each sweep and starts step i
+        const int f0 = i > 0 ? i - 1 : -1, f1 = i < K ? i : -1;
+        const int b0 = i > 0 ? K - i : -1, b1 = i < K ? K - 1 - i : -1;
+        const pft::MArgs<T> m0 = margs<T>(c, f0, f1, nullptr, slice<T>(c->qs, c, i));
+        const pft::MArgs<T> m1 = margs<T>(c, b0, b1, nullptr, slice<T>(c->qds, c, i), wb);
+        ProfScope ps(c, PFT_K_YZPASS, zbytes(c, f0, f1, false, true, false) + zbytes(c, b0, b1, false, true, false), nullptr,
+                     true);
+        PFT_HIP(c, pft::launch_myz<T>(c->p.ny, m0, m1, 2, c->stream));
+        return PFT_OK;
+    };
+    pft_status s = yz(0);
+    for (int i = 0; i < K && !s; ++i) {
+        {
+            ProfScope ps(c, PFT_K_XPASS, 2 * xbytes(c, false, false), nullptr, true);
+            PFT_HIP(c, pft::launch_mx<T>(c->p.nx, mxargs<T>(c, i), mxargs<T>(c, K - 1 - i, wb), 2, c->stream));
+        }
+        s = yz(i + 1);
+    }
+    return s;
+}
+
 template <typename T>
 pft_status field_tables_t(pft_ctx* c, const double* wp, const double* wm)
 {
@@ -473,33 +593,6 @@ pft::ZArgs<T> zargs(const pft_ctx* c, int prev, int next, const cx<T>* qin, cx<T
         a.En = etab<T>(c, c->kind[next]);
         a.gh_n = gptr<T>(c, c->hid[next], 0, 2);
         a.gf_n = gptr<T>(c, c->hid[next], 1, 2);
-    }
-    return a;
-}
-
-template <typename T>
-pft::PArgs<T> pargs(const pft_ctx* c, int prev, int next, const cx<T>* qin, cx<T>* qout)
-{
-    pft::PArgs<T> a{};
-    a.nplanes = c->p.nx;
-    a.U = static_cast<cx<T>*>(c->U);
-    a.V = static_cast<cx<T>*>(c->V);
-    a.qin = qin;
-    a.qout = qout;
-    a.scheme = c->p.scheme;
-    a.has_prev = prev >= 0;
-    a.has_next = next >= 0;
-    if (prev >= 0) {
-        a.Ep = etab<T>(c, c->kind[prev]);
-        a.gyh_p = gptr<T>(c, c->hid[prev], 0, 1);
-        a.gzh_p = gptr<T>(c, c->hid[prev], 0, 2);
-    }
-    if (next >= 0) {
-        a.En = etab<T>(c, c->kind[next]);
-        a.gzh_n = gptr<T>(c, c->hid[next], 0, 2);
-        a.gzf_n = gptr<T>(c, c->hid[next], 1, 2);
-        a.gyh_n = gptr<T>(c, c->hid[next], 0, 1);
-        a.gyf_n = gptr<T>(c, c->hid[next], 1, 1);
     }
     return a;
 }

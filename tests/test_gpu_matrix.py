@@ -1,0 +1,70 @@
+"""Line diffusions on the matrix cores (the x pass and the fused yz pass of
+square planes up to 64): every x length beside a plane, both precisions,
+against the oracle, with a junction sub-step; both sweeps in shared launches
+equal to sweeps one after the other; the same x pass by line transforms.
+
+Bars: those of the other passes (complex double |dphi| <= 1e-10 and Q 1e-11
+relative; complex float 2e-5)."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1204_5434_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+LENGTHS = {B.PFT_C128: (8, 12, 16, 20, 24, 32, 40, 48, 64, 80), B.PFT_C64: (8, 12, 16, 20, 24, 32, 40, 48, 64, 80, 96)}
+CASES = [(prec, nx) for prec in LENGTHS for nx in LENGTHS[prec]]
+
+
+def evaluate(ctx, wp, wm):
+    return {k: v.cpu().numpy() for k, v in ctx.evaluate(wp, wm).items()}
+
+
+@pytest.mark.parametrize("prec,nx", CASES, ids=[f"{'c128' if p == 0 else 'c64'}-{n}" for p, n in CASES])
+def test_every_x_length(orc, prec, nx):
+    side = (12, 20, 24, 8)[nx // 4 % 4]  # planes that share a workgroup, and ones that do not
+    n, L, ns, f = (nx, side, side), (0.12 * nx, 0.13 * side, 0.1 * side), 9, 0.37
+    print("matrix passes", prec, n, flush=True)
+    r = np.random.default_rng(nx)
+    wp, wm = (0.4 * r.standard_normal(n) + 0.1j * r.standard_normal(n) for _ in range(2))
+    ref = orc.evaluate(orc.Params(*n, *L, ns, f, 15.0, 2.0, 0, False), wp, wm)
+    gp, gm = torch.from_numpy(wp).to(DEV), torch.from_numpy(wm).to(DEV)
+    ctx = B.Context(B.Params(*n, *L, ns, f, 15.0, 2.0, prec, 0))
+    assert ctx.pft_fused_planes() == 1
+    got = evaluate(ctx, gp, gm)
+    ctx.pft_set_concurrent_sweeps(False)
+    alone = evaluate(ctx, gp, gm)
+    ctx.pft_set_variant(0, 0)
+    lines = evaluate(ctx, gp, gm)
+    ctx.close()
+    tol, tq = (1e-10, 1e-11) if prec == B.PFT_C128 else (2e-5, 2e-5)
+    for key in ("phiA", "phiB", "Q"):
+        assert np.array_equal(got[key], alone[key]), key
+    for o in (got, lines):
+        for key in ("phiA", "phiB"):
+            assert np.abs(o[key] - ref[key]).max() <= tol * max(1.0, np.abs(ref[key]).max()), key
+        assert abs(o["Q"][0] - ref["Q"]) <= tq * abs(ref["Q"])
+
+
+@pytest.mark.parametrize("prec", [B.PFT_C128, B.PFT_C64])
+def test_constant_and_nonfinite_fields(prec):
+    """A uniform field leaves q uniform (its closed form, Eq. (5)); a field
+    that is not finite at one site reaches the status flag."""
+    n, ns, w = (16, 32, 32), 12, 0.7
+    ctx = B.Context(B.Params(*n, 2.0, 4.0, 4.0, ns, 0.5, 15.0, 1.0, prec, 0))
+    wp = torch.zeros(n, dtype=torch.complex128, device=DEV)
+    wm = torch.full(n, w, dtype=torch.complex128, device=DEV)
+    out = ctx.evaluate(wp, wm)
+    # w_A = -w, w_B = w, f = 1/2: Q = 1 and phi_A = 1/2
+    tol = 1e-13 if prec == B.PFT_C128 else 2e-6
+    assert abs(out["Q"].item() - 1.0) <= tol
+    assert ctx.pft_status_flags() == 0
+    for bad in (float("inf"), float("nan")):
+        c2 = B.Context(B.Params(*n, 2.0, 4.0, 4.0, ns, 0.5, 15.0, 1.0, prec, 0))
+        w2 = wm.clone()
+        w2[3, 5, 7] = -bad
+        c2.evaluate(wp, w2)
+        assert c2.pft_status_flags() & 1
+        c2.close()
+    ctx.close()
