@@ -6,6 +6,22 @@
 
 namespace {
 
+// Keeps a context's own axis passes off the matrix cores while it lives.
+struct MatrixOff {
+    pft_ctx* c;
+    bool m[3];
+    MatrixOff(pft_ctx* ctx, bool off) : c(ctx), m{ctx->m[0], ctx->m[1], ctx->m[2]}
+    {
+        for (bool& x : c->m) x = x && !off;
+    }
+    ~MatrixOff()
+    {
+        for (int a = 0; a < 3; ++a) c->m[a] = m[a];
+    }
+    MatrixOff(const MatrixOff&) = delete;
+    MatrixOff& operator=(const MatrixOff&) = delete;
+};
+
 // ---------------------------------------------------------------- adjoint --
 // Reverse mode through the K split steps.  The forward sweep keeps q only at
 // the checkpoint nodes 0, Kc, 2Kc, ... and q_K.  The adjoint vector of step j
@@ -21,6 +37,18 @@ pft_status adjoint_t(pft_ctx* c, const double* wp, const double* wm, int Kc, dou
     const int K = c->K;
     const int64_t M = c->M;
     const bool rqm4 = c->p.scheme == PFT_RQM4;
+    // Complex double runs the fused pass where it is on the matrix cores, two
+    // launches a step.  Complex float stays with the line transforms: near a
+    // saddle point dH/dw is what is left of cancelling terms, and the rounding of
+    // the passes is 1e-5 of it.
+    const MatrixOff keep(c, std::is_same<T, float>::value);
+    const bool planes = std::is_same<T, double>::value && c->mplane && c->m[0] && c->fused;
+    auto ends = [&](int prev, int next, const cx<T>* qin, cx<T>* qout, const Work& w = Work(), cx<T>* hcap = nullptr) {
+        return planes ? yzpass<T>(c, prev, next, qin, qout, w, hcap) : zpass<T>(c, prev, next, qin, qout, w, hcap);
+    };
+    auto body = [&](int j, const Work& w = Work(), cx<T>* capA = nullptr, cx<T>* capC = nullptr) {
+        return planes ? xpass_step<T>(c, j, w, capA, capC) : step_body<T>(c, j, w, capA, capC);
+    };
     const int nck = (K + Kc - 1) / Kc;  // checkpoint nodes a = 0, Kc, ... < K
     // the segment buffers are doubled when the next segment's recomputation
     // runs on the second stream beside the current segment's adjoint steps
@@ -89,14 +117,14 @@ pft_status adjoint_t(pft_ctx* c, const double* wp, const double* wm, int Kc, dou
     pft_status s = field_tables_t<T>(c, wp, wm);
     if (s) return s;
     // forward sweep keeping checkpoints
-    s = zpass<T>(c, -1, 0, nullptr, ckpt(0));
+    s = ends(-1, 0, nullptr, ckpt(0));
     if (s) return s;
     for (int i = 0; i < K; ++i) {
-        s = step_body<T>(c, i);
+        s = body(i);
         if (s) return s;
         const int node = i + 1;
         cx<T>* out = node == K ? qK : (node % Kc == 0 ? ckpt(node) : nullptr);
-        s = zpass<T>(c, i, i + 1 < K ? i + 1 : -1, nullptr, out);
+        s = ends(i, i + 1 < K ? i + 1 : -1, nullptr, out);
         if (s) return s;
     }
     hipLaunchKernelGGL((k_sum_partials<T>), dim3(c->nparts), dim3(kRedThreads), 0, c->stream, qK, M, c->partials);
@@ -120,12 +148,12 @@ pft_status adjoint_t(pft_ctx* c, const double* wp, const double* wm, int Kc, dou
     const Work wr{c->U, c->V, rs};
     auto recompute = [&](int sg) -> pft_status {
         const int a0 = sg * Kc, b0 = std::min(a0 + Kc, K), bf = sg % 2;
-        pft_status e = zpass<T>(c, -1, a0, ckpt(a0), nullptr, wr);
+        pft_status e = ends(-1, a0, ckpt(a0), nullptr, wr);
         if (e) return e;
         for (int jj = a0; jj < b0; ++jj) {
-            e = step_body<T>(c, jj, wr, rqm4 ? seg(segA[bf], jj - a0) : nullptr, rqm4 ? seg(segC[bf], jj - a0) : nullptr);
+            e = body(jj, wr, rqm4 ? seg(segA[bf], jj - a0) : nullptr, rqm4 ? seg(segC[bf], jj - a0) : nullptr);
             if (e) return e;
-            e = zpass<T>(c, jj, jj + 1 < b0 ? jj + 1 : -1, nullptr, seg(segQ[bf], jj - a0), wr, seg(segB[bf], jj - a0));
+            e = ends(jj, jj + 1 < b0 ? jj + 1 : -1, nullptr, seg(segQ[bf], jj - a0), wr, seg(segB[bf], jj - a0));
             if (e) return e;
         }
         PFT_HIP(c, hipEventRecord(c->ev_adj[bf], rs));  // ready
@@ -139,7 +167,7 @@ pft_status adjoint_t(pft_ctx* c, const double* wp, const double* wm, int Kc, dou
     }
 
     // lambda_K = 1, then the steps in reverse order
-    s = zpass<T>(c, -1, K - 1, nullptr, lam[0], wl);
+    s = ends(-1, K - 1, nullptr, lam[0], wl);
     if (s) return s;
     int cur = 0;
     for (int j = K - 1; j >= 0; --j) {
@@ -164,9 +192,9 @@ pft_status adjoint_t(pft_ctx* c, const double* wp, const double* wm, int Kc, dou
         cx<T>* const sA = segA[bf];
         cx<T>* const sB = segB[bf];
         cx<T>* const sC = segC[bf];
-        s = step_body<T>(c, j, wl, rqm4 ? Al : nullptr, nullptr);
+        s = body(j, wl, rqm4 ? Al : nullptr, nullptr);
         if (s) return s;
-        s = zpass<T>(c, j, j > 0 ? j - 1 : -1, nullptr, lam[1 - cur], wl, rqm4 ? Bl : nullptr);
+        s = ends(j, j > 0 ? j - 1 : -1, nullptr, lam[1 - cur], wl, rqm4 ? Bl : nullptr);
         if (s) return s;
         const cx<T>* q0 = (j == a) ? ckpt(a) : seg(sQ, j - a - 1);
         AccArgs<T> ac{lam[cur], lam[1 - cur], Al, Bl, q0, seg(sQ, j - a), seg(sA, j - a), seg(sB, j - a),

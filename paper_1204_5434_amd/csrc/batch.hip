@@ -24,12 +24,13 @@ struct BatchGroup {
     int sp_axis[3] = {0, 0, 0};
     int var[3] = {0, 0, 0};      // kernel variants (x, y, z) of the group's grid
     bool fused = false;          // fused yz-plane schedule: zd holds PArgs, sd the x passes only
-    bool mplane = false;         // ... on the matrix cores: zd holds MArgs
-    bool mx = false;             // ... and the x pass beside it: sd holds MXArgs
+    bool mz = false;             // the z or yz pass runs on the matrix cores: zd holds MArgs
+    bool ms[3] = {false, false, false};  // so does strided pass k: its arguments are in md
     hipStream_t s = nullptr;
     hipEvent_t done = nullptr;
     void* zd = nullptr;          // [dir 2][pos maxK+1][R] ZArgs (PArgs when fused)
     void* sd = nullptr;          // [dir 2][pos maxK][npass][R] SArgs
+    void* md = nullptr;          // [pos maxK][npass][dir 2][R] MXArgs
     void* jobs[2] = {nullptr, nullptr};  // job tables of the small kernels: [0] evaluations, [1] the captured field step
     size_t off_sisinc = 0, off_sis = 0;  // semi-implicit step: [R] SisIncArgs, [5 passes][R] SisArgs,
     size_t off_mirror = 0;               //   [R] MirrorJob (walled groups: the filter runs on the even image)
@@ -88,6 +89,7 @@ void batch_free(pft_batch* b)
         if (g.done) (void)hipEventDestroy(g.done);
         if (g.zd) (void)hipFree(g.zd);
         if (g.sd) (void)hipFree(g.sd);
+        if (g.md) (void)hipFree(g.md);
         for (void* j : g.jobs)
             if (j) (void)hipFree(j);
     }
@@ -100,40 +102,48 @@ void batch_free(pft_batch* b)
     for (pft_ctx* c : b->ctx) pft_destroy(c);
 }
 
-// Argument tables of one group's passes for both sweeps and every sweep
-// position, laid out [position][sweep][replica], where they run on the matrix
-// cores.
+// Argument tables of a group's passes on the matrix cores, for both sweeps and
+// every sweep position.
 template <typename T>
 pft_status batch_build_m_tables(pft_batch* b, BatchGroup& g)
 {
     const int R = (int)g.reps.size(), D = g.ndir;
-    std::vector<pft::MArgs<T>> zd((size_t)D * (g.maxK + 1) * R);
-    std::vector<pft::MXArgs<T>> xd(g.mx ? (size_t)D * g.maxK * R : 0);
+    std::vector<pft::MArgs<T>> zd(g.mz ? (size_t)D * (g.maxK + 1) * R : 0);
+    std::vector<pft::MXArgs<T>> md(g.ms[0] || g.ms[1] ? (size_t)D * g.maxK * g.npass * R : 0);
     for (int dir = 0; dir < D; ++dir)
         for (int ri = 0; ri < R; ++ri) {
             pft_ctx* c = b->ctx[g.reps[ri]];
             const int K = c->K;
+            const bool rqm4 = c->p.scheme == PFT_RQM4;
             auto stepj = [&](int i) { return dir ? K - 1 - i : i; };
             void* store = dir ? c->qds : c->qs;
+            // the two sweeps advance in the same launches, so each has its own work pair
             const Work w{dir ? c->U2 : c->U, dir ? c->V2 : c->V, nullptr};
             for (int p = 0; p <= g.maxK; ++p) {
-                const size_t at = ((size_t)p * D + dir) * R + ri;
-                if (p > K)
-                    zd[at].skip = 1;
-                else
-                    zd[at] = margs<T>(c, p > 0 ? stepj(p - 1) : -1, p < K ? stepj(p) : -1, nullptr, slice<T>(store, c, p), w);
-                if (!g.mx || p >= g.maxK) continue;
-                if (p >= K)
-                    xd[at].skip = 1;
-                else
-                    xd[at] = mxargs<T>(c, stepj(p), w);
+                if (!zd.empty()) {
+                    pft::MArgs<T>& d = zd[((size_t)p * D + dir) * R + ri];
+                    if (p > K)
+                        d.skip = 1;
+                    else
+                        d = margs<T>(c, p > 0 ? stepj(p - 1) : -1, p < K ? stepj(p) : -1, nullptr, slice<T>(store, c, p), w);
+                }
+                for (int k = 0; k < g.npass && p < g.maxK && !md.empty(); ++k) {
+                    pft::MXArgs<T>& d = md[(((size_t)p * g.npass + k) * D + dir) * R + ri];
+                    if (p >= K)
+                        d.skip = 1;
+                    else
+                        d = g.sp_axis[k] == 0 ? mxargs<T>(c, stepj(p), w) : myargs<T>(c, stepj(p), rqm4, k == 0, w);
+                }
             }
         }
-    PFT_BHIP(b, hipMalloc(&g.zd, zd.size() * sizeof(zd[0])));
-    PFT_BHIP(b, hipMemcpy(g.zd, zd.data(), zd.size() * sizeof(zd[0]), hipMemcpyHostToDevice));
-    if (!g.mx) return PFT_OK;
-    PFT_BHIP(b, hipMalloc(&g.sd, xd.size() * sizeof(xd[0])));
-    PFT_BHIP(b, hipMemcpy(g.sd, xd.data(), xd.size() * sizeof(xd[0]), hipMemcpyHostToDevice));
+    if (!zd.empty()) {
+        PFT_BHIP(b, hipMalloc(&g.zd, zd.size() * sizeof(zd[0])));
+        PFT_BHIP(b, hipMemcpy(g.zd, zd.data(), zd.size() * sizeof(zd[0]), hipMemcpyHostToDevice));
+    }
+    if (!md.empty()) {
+        PFT_BHIP(b, hipMalloc(&g.md, md.size() * sizeof(md[0])));
+        PFT_BHIP(b, hipMemcpy(g.md, md.data(), md.size() * sizeof(md[0]), hipMemcpyHostToDevice));
+    }
     return PFT_OK;
 }
 
@@ -142,14 +152,15 @@ pft_status batch_build_m_tables(pft_batch* b, BatchGroup& g)
 template <typename T>
 pft_status batch_build_pass_tables(pft_batch* b, BatchGroup& g)
 {
-    if (g.mplane) {
-        const pft_status s = batch_build_m_tables<T>(b, g);
-        if (s || g.mx) return s;
-    }
+    const pft_status ms = batch_build_m_tables<T>(b, g);
+    if (ms) return ms;
+    bool strided = false;  // passes left to the line transforms
+    for (int k = 0; k < g.npass; ++k) strided = strided || !g.ms[k];
+    if (g.mz && !strided) return PFT_OK;
     const int R = (int)g.reps.size();
     const int D = g.ndir;
-    std::vector<pft::ZArgs<T>> zd(g.fused ? 0 : (size_t)D * (g.maxK + 1) * R);
-    std::vector<pft::PArgs<T>> pd(g.fused && !g.mplane ? (size_t)D * (g.maxK + 1) * R : 0);
+    std::vector<pft::ZArgs<T>> zd(g.fused || g.mz ? 0 : (size_t)D * (g.maxK + 1) * R);
+    std::vector<pft::PArgs<T>> pd(g.fused && !g.mz ? (size_t)D * (g.maxK + 1) * R : 0);
     std::vector<pft::SArgs<T>> sd((size_t)D * g.maxK * g.npass * R);
     for (int dir = 0; dir < g.ndir; ++dir)
         for (int ri = 0; ri < R; ++ri) {
@@ -164,7 +175,7 @@ pft_status batch_build_pass_tables(pft_batch* b, BatchGroup& g)
                 const int i = p - 1;  // Z (or yz) at position p completes step i and starts step i + 1
                 const size_t at = ((size_t)p * D + dir) * R + ri;
                 const int prev = i >= 0 ? stepj(i) : -1, next = i + 1 < K ? stepj(i + 1) : -1;
-                if (g.mplane) {
+                if (g.mz) {
                     continue;
                 } else if (g.fused) {
                     if (i >= K) {
@@ -203,7 +214,7 @@ pft_status batch_build_pass_tables(pft_batch* b, BatchGroup& g)
                 }
             }
         }
-    if (!g.mplane) {
+    if (!g.mz) {
         const size_t zbytes = g.fused ? pd.size() * sizeof(pd[0]) : zd.size() * sizeof(zd[0]);
         PFT_BHIP(b, hipMalloc(&g.zd, zbytes));
         PFT_BHIP(b, hipMemcpy(g.zd, g.fused ? (const void*)pd.data() : (const void*)zd.data(), zbytes,
@@ -355,18 +366,23 @@ pft_status batch_enqueue_group(pft_batch* b, BatchGroup& g, int slot, bool updat
     // the z pass, or the fused yz pass, at sweep position p
     auto zlaunch = [&](int p) -> hipError_t {
         const size_t at = (size_t)p * DR;
-        if (g.mplane) return pft::launch_myz_batch<T>(g.ny, g.nx, static_cast<const pft::MArgs<T>*>(g.zd) + at, DR, s);
+        const pft::MArgs<T>* md = static_cast<const pft::MArgs<T>*>(g.zd) + at;
+        if (g.mz && g.fused) return pft::launch_myz_batch<T>(g.ny, g.nx, md, DR, s);
+        if (g.mz) return pft::launch_mz_batch<T>(g.nz, g.bc[2] != 0, (int)nlines, md, DR, s);
         if (g.fused) return pft::launch_yzpass_batch<T>(g.ny, g.nx, pd + at, DR, s);
         if (g.bc[2]) return pft::launch_zpass_walls_batch<T>(g.nz, g.bc[2], nlines, zd + at, DR, s);
         return pft::launch_zpass_batch<T>(g.nz, g.var[2], nlines, zd + at, DR, s);
     };
     PFT_BHIP(b, zlaunch(0));
     for (int p = 0; p < g.maxK; ++p) {
-        if (g.mx)
-            PFT_BHIP(b, pft::launch_mx_batch<T>(g.nx, g.ny * g.nz,
-                                                static_cast<const pft::MXArgs<T>*>(g.sd) + (size_t)p * DR, DR, s));
-        for (int k = 0; k < g.npass && !g.mx; ++k) {
+        for (int k = 0; k < g.npass; ++k) {
             const int ax = g.sp_axis[k];
+            if (g.ms[k]) {
+                PFT_BHIP(b, pft::launch_mx_batch<T>(n_ax[ax], g.bc[ax] != 0, (int)(ncols[ax] * nslabs[ax]),
+                                                    static_cast<const pft::MXArgs<T>*>(g.md) + ((size_t)p * g.npass + k) * DR,
+                                                    DR, s));
+                continue;
+            }
             const pft::SArgs<T>* at = sd + ((size_t)p * g.npass + k) * DR;
             if (g.bc[ax])
                 PFT_BHIP(b, pft::launch_spass_walls_batch<T>(ax, n_ax[ax], g.bc[ax], ncols[ax], nslabs[ax], at, DR, s));
@@ -605,8 +621,6 @@ pft_status pft_batch_create(const pft_params* params, int32_t n, void* hip_strea
             for (int a = 0; a < 3; ++a) g->bc[a] = p.bc[a];
             g->ndir = p.model == PFT_EDWARDS ? 1 : 2;
             g->fused = fused;
-            g->mplane = fused && b->ctx[r]->mplane;
-            g->mx = g->mplane && b->ctx[r]->mx;
             if (g->fused) {
                 g->npass = 1;  // the x pass; the y and z work runs in the yz pass
                 g->sp_axis[0] = 0;
@@ -615,6 +629,8 @@ pft_status pft_batch_create(const pft_params* params, int32_t n, void* hip_strea
                 const int ax3[3] = {1, 0, 1};
                 for (int k = 0; k < 3; ++k) g->sp_axis[k] = ax3[k];
             }
+            g->mz = fused ? b->ctx[r]->mplane : b->ctx[r]->m[2];
+            for (int k = 0; k < g->npass; ++k) g->ms[k] = b->ctx[r]->m[g->sp_axis[k]];
         }
         g->reps.push_back(r);
         for (int a = 0; a < 3; ++a) g->var[a] = b->ctx[g->reps[0]]->var[a];

@@ -140,7 +140,7 @@ pft_status propagate_t(pft_ctx* c, const double* wp, const double* wm)
         // symmetric chain: q-dagger = q, one sweep
         s = sweep<T>(c, false, c->qs);
         if (s) return s;
-    } else if (c->together && c->fused && !c->fused_conj_only && c->mx && c->s2 && !c->dual_off) {
+    } else if (c->together && !c->fused_conj_only && all_matrix(c) && c->s2 && !c->dual_off) {
         // small grids: launches and latency count, so both sweeps share each launch
         s = sweeps_together<T>(c);
         if (s) return s;
@@ -430,19 +430,20 @@ pft_status upload_matrices(pft_ctx* c)
         if (hd > 0 && !(c->hval[hd] > 0)) continue;  // no junction sub-steps
         for (int full = 0; full < 2; ++full)
             for (int ax = 0; ax < 3; ++ax) {
-                if (ax == 0 ? !c->mx : !c->mplane) continue;
+                if (c->moff[ax + 1] == c->moff[ax]) continue;
                 T* out = tab.data() + (size_t)(hd * 2 + full) * c->moff[3] + c->moff[ax];
-                if (ax == 2 && n[2] == n[1] && L[2] == L[1]) {
-                    std::copy_n(out - (c->moff[2] - c->moff[1]), c->moff[2] - c->moff[1], out);
+                const int bc = c->p.bc[ax], pr = ax - 1;
+                if (pr >= 0 && n[pr] == n[ax] && L[pr] == L[ax] && c->p.bc[pr] == bc && c->moff[ax] > c->moff[pr]) {
+                    std::copy_n(out - (c->moff[ax] - c->moff[pr]), c->moff[ax] - c->moff[pr], out);
                     continue;
                 }
-                std::vector<double> g(n[ax]);
-                for (int j = 0; j < n[ax]; ++j) {
-                    const int m = (j <= n[ax] / 2) ? j : j - n[ax];
-                    const double k = kTwoPi * m / L[ax];
+                std::vector<double> g(n[ax] + 1);
+                for (int j = 0; j <= n[ax]; ++j) {
+                    const int m = bc ? j : (j <= n[ax] / 2) ? j : j - n[ax];
+                    const double k = (bc ? kPi : kTwoPi) * m / L[ax];
                     g[j] = std::exp(-k * k * (full ? c->hval[hd] : c->hval[hd] / 2));
                 }
-                pft::mtable<T>(n[ax], g, out);
+                pft::mtable<T>(n[ax], bc, g, out);
             }
     }
     PFT_HIP(c, hipMemcpy(c->mtab, tab.data(), tab.size() * sizeof(T), hipMemcpyHostToDevice));
@@ -502,8 +503,13 @@ constexpr int kFusedMaxSpill = 256;
 // ms), with 248 (absorbing walls on y and z) it loses (12.39 against 11.85).
 constexpr int kFusedMaxSpillWalls = 128;
 
-// Grids up to this many sites run both sweeps in the same launches.
-constexpr int64_t kTogetherMax = 64 * 64 * 64;
+// Both sweeps share each launch while one array of the grid is smaller than
+// this, where launches and latency count: the launches of two streams and their
+// gaps cost more than one stream's passes leave idle (us per contour step, two
+// streams against shared launches: 32^3 complex float 14.3 / 12.0, 64 x 48 x 80
+// 46.4 / 40.1, complex double 53.4 / 50.9; at 64^3 complex double, 4 MiB, 32.1 /
+// 35.5).
+constexpr int64_t kTogetherBytes = 4 << 20;
 
 // Walls along y or z have a fused pass in complex float only.
 static bool fused_supported(const pft_params& p)
@@ -564,14 +570,25 @@ pft_status create_ctx(const pft_params* params, void* hip_stream, bool dual, pft
     const bool dbl = p.precision == PFT_C128;
     c->mplane = p.ny == p.nz && !p.bc[1] && !p.bc[2] &&
                 (dbl ? pft::mplane_supported<double>(p.ny) : pft::mplane_supported<float>(p.ny));
-    c->mx = c->mplane && !p.bc[0] && (dbl ? pft::mx_supported<double>(p.nx) : pft::mx_supported<float>(p.nx));
-    c->fused = c->mplane || fused_default(p);
-    c->together = (int64_t)p.nx * p.ny * p.nz <= kTogetherMax;
-    c->stream = static_cast<hipStream_t>(hip_stream);
+    c->elem = p.precision == PFT_C128 ? sizeof(cx<double>) : sizeof(cx<float>);
     c->M = (int64_t)p.nx * p.ny * p.nz;
+    c->together = c->M * (int64_t)c->elem < kTogetherBytes;
+    for (int ax = 0; ax < 3; ++ax) {
+        const int na = ax == 0 ? p.nx : ax == 1 ? p.ny : p.nz;
+        const bool wall = p.bc[ax] != 0;
+        c->m[ax] = ax < 2 ? (dbl ? pft::mx_supported<double>(na, wall) : pft::mx_supported<float>(na, wall))
+                          : (dbl ? pft::mz_supported<double>(na, wall) : pft::mz_supported<float>(na, wall));
+    }
+    // Long periodic z lines lose to the line transforms (z pass, us: complex float
+    // 48 points 10.0 / 7.2, 80 points 14.1 / 13.8; complex double 64 points 11.2 /
+    // 12.3, 80 points 17.2 / 17.2; between walls 80 points 15.7 / 19.6 and 16.0 /
+    // 25.1), unless that lets a small grid share its launches.
+    if (!p.bc[2] && !c->together && p.nz > (dbl ? 64 : 40)) c->m[2] = false;
+    // between walls the axis passes on the matrix cores beat the line transforms' fused pass
+    c->fused = c->mplane || (!((p.bc[1] || p.bc[2]) && c->m[1] && c->m[2]) && fused_default(p));
+    c->stream = static_cast<hipStream_t>(hip_stream);
     // table slot length: n factors per periodic axis, 3n per walled axis
     c->maxN = std::max((p.bc[0] ? 3 : 1) * p.nx, std::max((p.bc[1] ? 3 : 1) * p.ny, (p.bc[2] ? 3 : 1) * p.nz));
-    c->elem = p.precision == PFT_C128 ? sizeof(cx<double>) : sizeof(cx<float>);
     c->h.resize(p.ns + 1);
     c->blk.resize(p.ns + 1);
     if (ed) {
@@ -612,7 +629,7 @@ pft_status create_ctx(const pft_params* params, void* hip_stream, bool dual, pft
     {
         const int n[3] = {p.nx, p.ny, p.nz};
         for (int ax = 0; ax < 3; ++ax)
-            c->moff[ax + 1] = c->moff[ax] + ((ax == 0 ? c->mx : c->mplane) ? pft::MSplitRt(n[ax]).size() : 0);
+            c->moff[ax + 1] = c->moff[ax] + (c->m[ax] || (ax > 0 && c->mplane) ? pft::MSplitRt(n[ax], p.bc[ax] != 0).size() : 0);
     }
     auto alloc = [&](void** ptr, size_t bytes) -> bool { return hipMalloc(ptr, std::max<size_t>(bytes, 16)) == hipSuccess; };
     const size_t store = (size_t)(c->K + 1) * c->M * c->elem;

@@ -12,7 +12,9 @@
 // i - j only and is even, so it commutes with the shift by N/2 and with the
 // reflection n -> N - 1 - n.  With x_n +- x_{n+N/2} it splits into two
 // matrices of N/2 points (2 ways), and with the reflection of each into four
-// of N/4 (4 ways): N multiplications per point instead of 4 N.
+// of N/4 (4 ways): N multiplications per point instead of 4 N.  Between walls
+// (reflecting or absorbing) the matrix depends on i - j and i + j and keeps the
+// reflection only: halves.
 //
 // Layout.  A group is 16 lanes; the wavefront's four groups g hold the rows,
 // lane % 16 is the column.  The product's result sits in the lanes and
@@ -33,34 +35,46 @@ namespace pft {
 // The split with the fewest products: lengths whose quarter is a multiple of
 // four rows go 4 ways, else halves, and up to 20 points one dense product of
 // padded rows costs no more than two halves.
-template <int N>
+template <int N, bool WALL = false>
 struct MSplit {
-    static constexpr int ways = N <= 20 ? 1 : (N % 16 == 0 && N >= 48) ? 4 : 2;
+    static constexpr int ways = N <= 20 ? 1 : (!WALL && N % 16 == 0 && N >= 48) ? 4 : 2;
     static constexpr int S = N / ways;
     static_assert(S % 4 == 0, "rows must spread over the four groups");
     static constexpr int R = S / 4;
     static constexpr int RB = (R + 3) / 4;
     static constexpr int NR = N / 4;                       // rows a lane holds
-    static constexpr int kFrag = ways * RB * R * 64;       // table entries
+    static constexpr int kSums = ways * RB * R * 64;       // walls: row sums follow the matrices
+    static constexpr int kFrag = kSums + (WALL ? (S + 63) / 64 * 64 : 0);  // table entries
 };
 
-// Rows of a sub-matrix per precision, chosen by the product's result layout
-// and by the memory accesses along the line: complex float gives each lane R
-// consecutive points (16-byte accesses), complex double interleaves the groups
-// (four consecutive points of a line per instruction).
+// Row of a sub-matrix that group g holds in its register rr, chosen by the
+// accesses along a contiguous line.  Complex float: R consecutive points per
+// lane (64 points in complex float: z pass 9.4 us; eight consecutive points over
+// the groups per instruction, as below, 16.8 us).  Complex double: register
+// pairs of consecutive points, the groups side by side, eight points (128
+// bytes) per instruction; an odd last register takes the four rows left (z pass
+// of 64 points 13.7 us with four points per instruction, 11.2 us with eight).
 template <typename T>
 __host__ __device__ constexpr int mrow(int g, int rr, int R)
 {
-    return sizeof(T) == 4 ? g * R + rr : 4 * rr + g;
+    return sizeof(T) == 4 ? g * R + rr : rr < R / 2 * 2 ? 8 * (rr / 2) + 2 * g + rr % 2 : 4 * rr + g;
 }
 // The point of the line that sub-vector t holds in row m.
-template <int N>
+template <int N, bool WALL = false>
 __host__ __device__ constexpr int mpoint(int t, int m)
 {
-    constexpr int W = MSplit<N>::ways;
+    constexpr int W = MSplit<N, WALL>::ways;
+    if (WALL && W == 2) return t == 0 ? m : N - 1 - m;
     if (W == 4) return t == 0 ? m : t == 1 ? N / 2 - 1 - m : t == 2 ? N / 2 + m : N - 1 - m;
     if (W == 2) return t == 0 ? m : N / 2 + m;
     return m;
+}
+
+// Whether sub-vector t runs against the line's direction.
+template <int N, bool WALL = false>
+constexpr bool mreversed(int t)
+{
+    return MSplit<N, WALL>::ways == 4 ? t % 2 == 1 : WALL && t == 1;
 }
 
 using mf4 = float __attribute__((ext_vector_type(4)));
@@ -73,10 +87,10 @@ __device__ __forceinline__ mf4 mprod(float a, float b, mf4 c) { return __builtin
 __device__ __forceinline__ md4 mprod(double a, double b, md4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
 
 // Sums and differences that split the line, and their inverse (scale in the table).
-template <int N, typename T>
+template <int N, bool WALL, typename T>
 __device__ __forceinline__ void msplit(T (&x)[N / 4])
 {
-    using M = MSplit<N>;
+    using M = MSplit<N, WALL>;
     constexpr int R = M::R;
     sfor<0, R>([&](auto I) {
         constexpr int i = decltype(I)::value;
@@ -94,10 +108,10 @@ __device__ __forceinline__ void msplit(T (&x)[N / 4])
         }
     });
 }
-template <int N, typename T>
+template <int N, bool WALL, typename T>
 __device__ __forceinline__ void mjoin(T (&x)[N / 4])
 {
-    using M = MSplit<N>;
+    using M = MSplit<N, WALL>;
     constexpr int R = M::R;
     sfor<0, R>([&](auto I) {
         constexpr int i = decltype(I)::value;
@@ -137,16 +151,18 @@ __device__ __forceinline__ double mlane(double x, int l)
 // direction, which shows as a drift of Q over the contour (4e-6 against 2e-7
 // in complex float over 100 steps at 64^3).
 // f: the matrix's table, [ways][RB][R][64 lanes], in LDS or global memory.
-template <int N, int NC, typename T>
+// Between walls the constant comes back times the row sums of the table
+// (absorbing walls do not keep it).
+template <int N, int NC, bool WALL = false, typename T>
 __device__ __forceinline__ void mdiffuse(T (&x)[NC][N / 4], const T* f)
 {
-    using M = MSplit<N>;
+    using M = MSplit<N, WALL>;
     constexpr int R = M::R, RB = M::RB;
     const int lane = threadIdx.x & 63;
     T mean[NC];  // `ways` times the constant: its share of the first sub-vector
     sfor<0, NC>([&](auto C) {
         constexpr int c = decltype(C)::value;
-        msplit<N>(x[c]);
+        msplit<N, WALL>(x[c]);
         if constexpr (NC == 2)
             mean[c] = mlane(x[c][0], 0);
         else
@@ -175,11 +191,16 @@ __device__ __forceinline__ void mdiffuse(T (&x)[NC][N / 4], const T* f)
             });
         });
     });
-    sfor<0, NC>([&](auto C) {
-        constexpr int c = decltype(C)::value;
-        sfor<0, R>([&](auto I) { x[c][decltype(I)::value] += mean[c] * T(1.0 / M::ways); });
-        mjoin<N>(x[c]);
+    sfor<0, R>([&](auto I) {
+        constexpr int i = decltype(I)::value;
+        T r;
+        if constexpr (WALL)
+            r = f[M::kSums + mrow<T>(lane >> 4, i, R)];
+        else
+            r = T(1.0 / M::ways);
+        sfor<0, NC>([&](auto C) { x[decltype(C)::value][i] += mean[decltype(C)::value] * r; });
     });
+    sfor<0, NC>([&](auto C) { mjoin<N, WALL>(x[decltype(C)::value]); });
 }
 
 // ------------------------------------------------- pairs of lanes (double) --

@@ -17,6 +17,7 @@
 
 #include "../../include/pft.h"
 #include "kernels.h"
+#include "maxis.h"
 #include "mplanes.h"
 #include "mtable.h"
 #include "ops.h"
@@ -53,7 +54,7 @@ struct pft_ctx {
     bool fused = false;               // sweeps use the fused yz-plane pass (square yz-plane in LDS)
     bool fused_conj_only = false;     // ... only the conjugate sweep (the forward one runs axis passes)
     bool mplane = false;              // the fused pass runs on the matrix cores
-    bool mx = false;                  // ... and so does the x pass beside it
+    bool m[3] = {false, false, false};  // ... and so does this axis's own pass (x, y, z)
     bool together = false;            // both sweeps advance in the same launches (small grids)
     size_t elem = 0;                  // bytes per propagator value
     // device buffers
@@ -226,45 +227,6 @@ hipError_t launch_z(const pft_ctx* c, const pft::ZArgs<T>& a, hipStream_t st)
     return pft::launch_zpass<T>(c->p.nz, c->var[2], a, st);
 }
 
-// Z pass completing step `prev` (-1: none) and starting step `next` (-1: none).
-template <typename T>
-pft_status zpass(pft_ctx* c, int prev, int next, const cx<T>* qin, cx<T>* qout, const Work& w = Work(),
-                 cx<T>* hcap = nullptr)
-{
-    pft::ZArgs<T> a{};
-    a.nlines = (int64_t)c->p.nx * c->p.ny;
-    a.U = static_cast<cx<T>*>(w.U ? w.U : c->U);
-    a.V = static_cast<cx<T>*>(w.V ? w.V : c->V);
-    a.hcap = hcap;
-    a.qin = qin;
-    a.qout = qout;
-    a.scheme = c->p.scheme;
-    a.has_prev = prev >= 0;
-    a.has_next = next >= 0;
-    if (prev >= 0) {
-        a.Ep = etab<T>(c, c->kind[prev]);
-        a.gh_p = gptr<T>(c, c->hid[prev], 0, 2);
-    }
-    if (next >= 0) {
-        a.En = etab<T>(c, c->kind[next]);
-        a.gh_n = gptr<T>(c, c->hid[next], 0, 2);
-        a.gf_n = gptr<T>(c, c->hid[next], 1, 2);
-    }
-    // algorithmic bytes: each distinct array read or written once
-    const double E = (double)c->elem * (double)c->M;
-    const bool rqm4 = c->p.scheme == PFT_RQM4;
-    double bytes = 0;
-    if (prev >= 0) bytes += (rqm4 ? 3 : 2) * E;
-    else if (qin) bytes += E;
-    if (qout) bytes += E;
-    if (next >= 0) bytes += (rqm4 ? 2 : 1) * E + ((prev < 0 || c->kind[next] != c->kind[prev]) ? E : 0);
-    if (hcap) bytes += E;
-    hipStream_t st = w.stream ? w.stream : c->stream;
-    ProfScope ps(c, PFT_K_ZPASS, bytes, st, c->p.bc[2] == 0);
-    PFT_HIP(c, launch_z<T>(c, a, st));
-    return PFT_OK;
-}
-
 // Strided pass along axis 0 (x) or 1 (y).
 template <typename T>
 pft_status spass(pft_ctx* c, int axis, pft::SOps<T> opU, pft::SOps<T> opV, const Work& w = Work())
@@ -299,6 +261,32 @@ pft_status spass(pft_ctx* c, int axis, pft::SOps<T> opU, pft::SOps<T> opV, const
             PFT_HIP(c, pft::launch_spass<T>(1, c->p.ny, c->var[1], c->p.nz, a, c->p.nx, st));
     }
     return PFT_OK;
+}
+
+// Argument sets of the passes, built without launching (the batched tables
+// hold one per replica and sweep position).
+template <typename T>
+pft::ZArgs<T> zargs(const pft_ctx* c, int prev, int next, const cx<T>* qin, cx<T>* qout)
+{
+    pft::ZArgs<T> a{};
+    a.nlines = (int64_t)c->p.nx * c->p.ny;
+    a.U = static_cast<cx<T>*>(c->U);
+    a.V = static_cast<cx<T>*>(c->V);
+    a.qin = qin;
+    a.qout = qout;
+    a.scheme = c->p.scheme;
+    a.has_prev = prev >= 0;
+    a.has_next = next >= 0;
+    if (prev >= 0) {
+        a.Ep = etab<T>(c, c->kind[prev]);
+        a.gh_p = gptr<T>(c, c->hid[prev], 0, 2);
+    }
+    if (next >= 0) {
+        a.En = etab<T>(c, c->kind[next]);
+        a.gh_n = gptr<T>(c, c->hid[next], 0, 2);
+        a.gf_n = gptr<T>(c, c->hid[next], 1, 2);
+    }
+    return a;
 }
 
 template <typename T>
@@ -349,6 +337,7 @@ pft::MArgs<T> margs(const pft_ctx* c, int prev, int next, const cx<T>* qin, cx<T
 {
     pft::MArgs<T> a{};
     a.nplanes = c->p.nx;
+    a.nlines = c->p.nx * c->p.ny;
     a.U = static_cast<cx<T>*>(w.U ? w.U : c->U);
     a.V = static_cast<cx<T>*>(w.V ? w.V : c->V);
     a.hcap = hcap;
@@ -377,7 +366,8 @@ pft::MXArgs<T> mxargs(const pft_ctx* c, int j, const Work& w = Work(), cx<T>* ca
 {
     const bool rqm4 = c->p.scheme == PFT_RQM4;
     pft::MXArgs<T> a{};
-    a.ncols = c->p.ny * c->p.nz;
+    a.ncols = a.width = c->p.ny * c->p.nz;
+    a.stride = a.ncols;
     a.U = rqm4 ? static_cast<cx<T>*>(w.U ? w.U : c->U) : nullptr;
     a.V = static_cast<cx<T>*>(w.V ? w.V : c->V);
     a.E = rqm4 ? etab<T>(c, c->kind[j]) : nullptr;
@@ -386,6 +376,42 @@ pft::MXArgs<T> mxargs(const pft_ctx* c, int j, const Work& w = Work(), cx<T>* ca
     a.capU = rqm4 ? capA : nullptr;
     a.capV = rqm4 ? capC : nullptr;
     return a;
+}
+
+// The y pass on both arrays (onU, onV), or one of them.
+template <typename T>
+pft::MXArgs<T> myargs(const pft_ctx* c, int j, bool onU, bool onV, const Work& w = Work())
+{
+    pft::MXArgs<T> a{};
+    a.ncols = c->p.nx * c->p.nz;
+    a.width = c->p.nz;
+    a.stride = c->p.nz;
+    a.slab_stride = (int64_t)c->p.ny * c->p.nz;
+    a.U = onU ? static_cast<cx<T>*>(w.U ? w.U : c->U) : nullptr;
+    a.V = onV ? static_cast<cx<T>*>(w.V ? w.V : c->V) : nullptr;
+    a.fh = mptr<T>(c, c->hid[j], 0, 1);
+    a.ff = mptr<T>(c, c->hid[j], 1, 1);
+    return a;
+}
+
+// Z pass completing step `prev` (-1: none) and starting step `next` (-1: none).
+template <typename T>
+pft_status zpass(pft_ctx* c, int prev, int next, const cx<T>* qin, cx<T>* qout, const Work& w = Work(),
+                 cx<T>* hcap = nullptr)
+{
+    hipStream_t st = w.stream ? w.stream : c->stream;
+    ProfScope ps(c, PFT_K_ZPASS, zbytes(c, prev, next, qin, qout, hcap), st, c->m[2] || c->p.bc[2] == 0);
+    if (c->m[2]) {
+        const pft::MArgs<T> m = margs<T>(c, prev, next, qin, qout, w, hcap);
+        PFT_HIP(c, pft::launch_mz<T>(c->p.nz, c->p.bc[2] != 0, m, m, 1, st));
+        return PFT_OK;
+    }
+    pft::ZArgs<T> a = zargs<T>(c, prev, next, qin, qout);
+    if (w.U) a.U = static_cast<cx<T>*>(w.U);
+    if (w.V) a.V = static_cast<cx<T>*>(w.V);
+    a.hcap = hcap;
+    PFT_HIP(c, launch_z<T>(c, a, st));
+    return PFT_OK;
 }
 
 // Fused yz-plane pass completing step `prev` (-1: none: its Y2 and Z) and
@@ -429,11 +455,11 @@ pft_status xpass_step(pft_ctx* c, int j, const Work& w = Work(), cx<T>* capA = n
 {
     const int hd = c->hid[j];
     const cx<T>* e = etab<T>(c, c->kind[j]);
-    if (c->mx) {
+    if (c->m[0]) {
         hipStream_t st = w.stream ? w.stream : c->stream;
         const pft::MXArgs<T> m = mxargs<T>(c, j, w, capA, capC);
         ProfScope ps(c, PFT_K_XPASS, xbytes(c, capA, capC), st, true);
-        PFT_HIP(c, pft::launch_mx<T>(c->p.nx, m, m, 1, st));
+        PFT_HIP(c, pft::launch_mx<T>(c->p.nx, c->p.bc[0] != 0, m, m, 1, st));
         return PFT_OK;
     }
     if (c->p.scheme == PFT_RQM4)
@@ -442,27 +468,35 @@ pft_status xpass_step(pft_ctx* c, int j, const Work& w = Work(), cx<T>* capA = n
     return spass<T>(c, 0, {nullptr, nullptr, nullptr}, {gptr<T>(c, hd, 1, 0), nullptr, nullptr}, w);
 }
 
+// The y pass of step j on both arrays (onU, onV), or one of them.
+template <typename T>
+pft_status ypass_step(pft_ctx* c, int j, bool onU, bool onV, const Work& w = Work())
+{
+    const int hd = c->hid[j];
+    if (c->m[1]) {
+        hipStream_t st = w.stream ? w.stream : c->stream;
+        const pft::MXArgs<T> m = myargs<T>(c, j, onU, onV, w);
+        ProfScope ps(c, PFT_K_YPASS, 2.0 * (onU + onV) * (double)c->elem * (double)c->M, st, true);
+        PFT_HIP(c, pft::launch_mx<T>(c->p.ny, c->p.bc[1] != 0, m, m, 1, st));
+        return PFT_OK;
+    }
+    const pft::SOps<T> none{nullptr, nullptr, nullptr};
+    return spass<T>(c, 1, onU ? pft::SOps<T>{gptr<T>(c, hd, 0, 1), nullptr, nullptr} : none,
+                    onV ? pft::SOps<T>{gptr<T>(c, hd, 1, 1), nullptr, nullptr} : none, w);
+}
+
 // The Y1, X, Y2 passes of step j (Y, X for the plain split).  capA / capC,
 // if set, receive D_{h/2} E4 q (half path after its first diffusion) and
 // D_h E2 q (full path before its last multiply) from the x pass.
 template <typename T>
 pft_status step_body(pft_ctx* c, int j, const Work& w = Work(), cx<T>* capA = nullptr, cx<T>* capC = nullptr)
 {
-    const int hd = c->hid[j];
-    const cx<T>* e = etab<T>(c, c->kind[j]);
-    const pft::SOps<T> none{nullptr, nullptr, nullptr};
-    pft_status s;
-    if (c->p.scheme == PFT_RQM4) {
-        s = spass<T>(c, 1, {gptr<T>(c, hd, 0, 1), nullptr, nullptr}, {gptr<T>(c, hd, 1, 1), nullptr, nullptr}, w);
-        if (s) return s;
-        s = spass<T>(c, 0, {gptr<T>(c, hd, 0, 0), e, gptr<T>(c, hd, 0, 0), capA},
-                     {gptr<T>(c, hd, 1, 0), e, nullptr, capC}, w);
-        if (s) return s;
-        return spass<T>(c, 1, {gptr<T>(c, hd, 0, 1), nullptr, nullptr}, none, w);
-    }
-    s = spass<T>(c, 1, none, {gptr<T>(c, hd, 1, 1), nullptr, nullptr}, w);
+    const bool rqm4 = c->p.scheme == PFT_RQM4;
+    pft_status s = ypass_step<T>(c, j, rqm4, true, w);
     if (s) return s;
-    return spass<T>(c, 0, none, {gptr<T>(c, hd, 1, 0), nullptr, nullptr}, w);
+    s = xpass_step<T>(c, j, w, capA, capC);
+    if (s || !rqm4) return s;
+    return ypass_step<T>(c, j, true, false, w);
 }
 
 // One sweep over the K steps, forward (q) or mirrored (q-dagger).  Node i
@@ -503,29 +537,43 @@ pft_status sweep(pft_ctx* c, bool backward, void* store, const Work& w = Work())
                           [](int) { return PFT_OK; });
 }
 
-// Both sweeps in the same launches, each on its own work pair.
+// Whether every pass of the current schedule runs on the matrix cores.
+inline bool all_matrix(const pft_ctx* c) { return c->fused ? c->mplane && c->m[0] : c->m[0] && c->m[1] && c->m[2]; }
+
+// Both sweeps in the same launches, each on its own work pair (all_matrix).
 template <typename T>
 pft_status sweeps_together(pft_ctx* c)
 {
     const int K = c->K;
+    const bool rqm4 = c->p.scheme == PFT_RQM4;
+    const double E = (double)c->elem * (double)c->M;
     const Work wb{c->U2, c->V2, nullptr};
-    auto yz = [&](int i) -> pft_status {  // completes step i - 1 of each sweep and starts step i
+    auto ends = [&](int i) -> pft_status {  // completes step i - 1 of each sweep and starts step i
         const int f0 = i > 0 ? i - 1 : -1, f1 = i < K ? i : -1;
         const int b0 = i > 0 ? K - i : -1, b1 = i < K ? K - 1 - i : -1;
         const pft::MArgs<T> m0 = margs<T>(c, f0, f1, nullptr, slice<T>(c->qs, c, i));
         const pft::MArgs<T> m1 = margs<T>(c, b0, b1, nullptr, slice<T>(c->qds, c, i), wb);
-        ProfScope ps(c, PFT_K_YZPASS, zbytes(c, f0, f1, false, true, false) + zbytes(c, b0, b1, false, true, false), nullptr,
-                     true);
-        PFT_HIP(c, pft::launch_myz<T>(c->p.ny, m0, m1, 2, c->stream));
+        ProfScope ps(c, c->fused ? PFT_K_YZPASS : PFT_K_ZPASS,
+                     zbytes(c, f0, f1, false, true, false) + zbytes(c, b0, b1, false, true, false), nullptr, true);
+        PFT_HIP(c, c->fused ? pft::launch_myz<T>(c->p.ny, m0, m1, 2, c->stream)
+                            : pft::launch_mz<T>(c->p.nz, c->p.bc[2] != 0, m0, m1, 2, c->stream));
         return PFT_OK;
     };
-    pft_status s = yz(0);
+    auto y = [&](int i, bool onV) -> pft_status {
+        ProfScope ps(c, PFT_K_YPASS, 4.0 * (rqm4 + onV) * E, nullptr, true);
+        PFT_HIP(c, pft::launch_mx<T>(c->p.ny, c->p.bc[1] != 0, myargs<T>(c, i, rqm4, onV),
+                                     myargs<T>(c, K - 1 - i, rqm4, onV, wb), 2, c->stream));
+        return PFT_OK;
+    };
+    pft_status s = ends(0);
     for (int i = 0; i < K && !s; ++i) {
+        if (!c->fused && (s = y(i, true))) return s;
         {
             ProfScope ps(c, PFT_K_XPASS, 2 * xbytes(c, false, false), nullptr, true);
-            PFT_HIP(c, pft::launch_mx<T>(c->p.nx, mxargs<T>(c, i), mxargs<T>(c, K - 1 - i, wb), 2, c->stream));
+            PFT_HIP(c, pft::launch_mx<T>(c->p.nx, c->p.bc[0] != 0, mxargs<T>(c, i), mxargs<T>(c, K - 1 - i, wb), 2, c->stream));
         }
-        s = yz(i + 1);
+        if (!c->fused && rqm4 && (s = y(i, false))) return s;
+        s = ends(i + 1);
     }
     return s;
 }
@@ -571,32 +619,7 @@ pft_status reduce_q(pft_ctx* c, const cx<T>* qK)
 // then the conjugate sweep, whose node i is paired at once with q_{K-i} and
 // added to the FP64 density accumulators (c->phi: A then B).
 
-// Argument sets of the passes, built without launching (the batched tables
-// hold one per replica and sweep position).
-template <typename T>
-pft::ZArgs<T> zargs(const pft_ctx* c, int prev, int next, const cx<T>* qin, cx<T>* qout)
-{
-    pft::ZArgs<T> a{};
-    a.nlines = (int64_t)c->p.nx * c->p.ny;
-    a.U = static_cast<cx<T>*>(c->U);
-    a.V = static_cast<cx<T>*>(c->V);
-    a.qin = qin;
-    a.qout = qout;
-    a.scheme = c->p.scheme;
-    a.has_prev = prev >= 0;
-    a.has_next = next >= 0;
-    if (prev >= 0) {
-        a.Ep = etab<T>(c, c->kind[prev]);
-        a.gh_p = gptr<T>(c, c->hid[prev], 0, 2);
-    }
-    if (next >= 0) {
-        a.En = etab<T>(c, c->kind[next]);
-        a.gh_n = gptr<T>(c, c->hid[next], 0, 2);
-        a.gf_n = gptr<T>(c, c->hid[next], 1, 2);
-    }
-    return a;
-}
-
+// Argument sets of the strided passes, as above.
 template <typename T>
 pft::SArgs<T> sargs(const pft_ctx* c, int axis, pft::SOps<T> opU, pft::SOps<T> opV)
 {

@@ -1,5 +1,6 @@
-"""Line diffusions on the matrix cores (the x pass and the fused yz pass of
-square planes up to 64): every x length beside a plane, both precisions,
+"""Line diffusions on the matrix cores (the axis passes, and the fused yz pass of
+square planes up to 64): every x length beside a plane, uneven grids and walls
+of both kinds on each axis length, both precisions,
 against the oracle, with a junction sub-step; both sweeps in shared launches
 equal to sweeps one after the other; the same x pass by line transforms.
 
@@ -45,6 +46,35 @@ def test_every_x_length(orc, prec, nx):
         for key in ("phiA", "phiB"):
             assert np.abs(o[key] - ref[key]).max() <= tol * max(1.0, np.abs(ref[key]).max()), key
         assert abs(o["Q"][0] - ref["Q"]) <= tq * abs(ref["Q"])
+
+
+# uneven grids: every length once along y and along z, walls of both kinds
+UNEVEN = [((16, 8, 12), (0, 0, 0), 0), ((12, 16, 8), (1, 2, 1), 0), ((8, 20, 16), (0, 1, 2), 0),
+          ((24, 12, 20), (2, 0, 0), 1), ((20, 32, 24), (1, 1, 0), 0), ((8, 24, 32), (0, 2, 1), 0),
+          ((12, 48, 40), (2, 1, 2), 0), ((40, 8, 48), (1, 0, 2), 0), ((8, 40, 64), (0, 2, 1), 1),
+          ((8, 64, 80), (0, 1, 2), 0), ((80, 12, 16), (2, 2, 1), 0), ((8, 80, 96), (0, 0, 0), 0), ((48, 96, 8), (1, 0, 1), 0)]
+
+
+@pytest.mark.parametrize("prec", [B.PFT_C128, B.PFT_C64])
+@pytest.mark.parametrize("n,bc,scheme", UNEVEN, ids=[f"{n}-{bc}" for n, bc, _ in UNEVEN])
+def test_uneven_grids_and_walls(orc, n, bc, scheme, prec):
+    L, ns, f = tuple(0.11 * a for a in n), 7, 0.41
+    print("matrix axis passes", prec, n, bc, scheme, flush=True)
+    r = np.random.default_rng(sum(n))
+    wp, wm = (0.4 * r.standard_normal(n) + 0.1j * r.standard_normal(n) for _ in range(2))
+    ref = orc.evaluate(orc.Params(*n, *L, ns, f, 15.0, 2.0, scheme, False, bc), wp, wm)
+    gp, gm = torch.from_numpy(wp).to(DEV), torch.from_numpy(wm).to(DEV)
+    ctx = B.Context(B.Params(*n, *L, ns, f, 15.0, 2.0, prec, scheme, B.PFT_DIBLOCK, 0.0, 0, bc))
+    got = evaluate(ctx, gp, gm)
+    ctx.pft_set_concurrent_sweeps(False)
+    alone = evaluate(ctx, gp, gm)
+    ctx.close()
+    tol, tq = (1e-10, 1e-11) if prec == B.PFT_C128 else (2e-5, 2e-5)
+    for key in ("phiA", "phiB", "Q"):
+        assert np.array_equal(got[key], alone[key]), key
+    for key in ("phiA", "phiB"):
+        assert np.abs(got[key] - ref[key]).max() <= tol * max(1.0, np.abs(ref[key]).max()), key
+    assert abs(got["Q"][0] - ref["Q"]) <= tq * abs(ref["Q"])
 
 
 @pytest.mark.parametrize("prec", [B.PFT_C128, B.PFT_C64])
