@@ -13,6 +13,14 @@
 // step of the whole batch is captured into a HIP graph and replayed.
 namespace {
 
+// Groups in flight at once, and the work and table arrays of one: four times
+// that stays in the 256 MB Infinity Cache.  256 replicas of 24^3 to 48^3 in
+// complex float, ms per field step: one group per shape 36.4, 24 MB 37.6, 32 MB
+// 34.6, 48 MB 34.1, 64 MB 33.8, 96 MB 35.5; two lanes of 64 MB 35.6; 64 replicas in
+// complex double 19.0, with 48 MB 18.2, with 64 MB 18.9.
+constexpr int kLanes = 4;
+constexpr double kGroupBytes = 48.0 * (1 << 20);
+
 struct BatchGroup {
     int nx = 0, ny = 0, nz = 0;
     int bc[3] = {0, 0, 0};       // walls of the group's replicas (fused groups have none on y and z)
@@ -26,8 +34,8 @@ struct BatchGroup {
     bool fused = false;          // fused yz-plane schedule: zd holds PArgs, sd the x passes only
     bool mz = false;             // the z or yz pass runs on the matrix cores: zd holds MArgs
     bool ms[3] = {false, false, false};  // so does strided pass k: its arguments are in md
-    hipStream_t s = nullptr;
-    hipEvent_t done = nullptr;
+    int lane = 0;
+    hipStream_t s = nullptr;     // the lane's stream
     void* zd = nullptr;          // [dir 2][pos maxK+1][R] ZArgs (PArgs when fused)
     void* sd = nullptr;          // [dir 2][pos maxK][npass][R] SArgs
     void* md = nullptr;          // [pos maxK][npass][dir 2][R] MXArgs
@@ -46,6 +54,9 @@ struct pft_batch {
     hipStream_t own = nullptr;     // the batch's stream: work is captured and replayed here
     std::vector<pft_ctx*> ctx;
     std::vector<BatchGroup> groups;
+    // groups run in lanes: those of one lane one after the other, on its stream
+    hipStream_t lane[kLanes] = {};
+    hipEvent_t done[kLanes] = {};
     hipEvent_t fork = nullptr;
     hipEvent_t in = nullptr, out = nullptr;  // joins with the caller's stream
     uint64_t* counters = nullptr;  // [0] Langevin step, [1] log row
@@ -85,13 +96,15 @@ void batch_free(pft_batch* b)
     if (b->exec) (void)hipGraphExecDestroy(b->exec);
     if (b->graph) (void)hipGraphDestroy(b->graph);
     for (BatchGroup& g : b->groups) {
-        if (g.s) (void)hipStreamDestroy(g.s);
-        if (g.done) (void)hipEventDestroy(g.done);
         if (g.zd) (void)hipFree(g.zd);
         if (g.sd) (void)hipFree(g.sd);
         if (g.md) (void)hipFree(g.md);
         for (void* j : g.jobs)
             if (j) (void)hipFree(j);
+    }
+    for (int l = 0; l < kLanes; ++l) {
+        if (b->lane[l]) (void)hipStreamDestroy(b->lane[l]);
+        if (b->done[l]) (void)hipEventDestroy(b->done[l]);
     }
     if (b->fork) (void)hipEventDestroy(b->fork);
     if (b->in) (void)hipEventDestroy(b->in);
@@ -100,6 +113,46 @@ void batch_free(pft_batch* b)
     if (b->counters) (void)hipFree(b->counters);
     if (b->logj) (void)hipFree(b->logj);
     for (pft_ctx* c : b->ctx) pft_destroy(c);
+}
+
+// Cuts the groups of one shape so that what is in flight stays in the Infinity
+// Cache: a contour step passes over every replica's work and table arrays, so a
+// group that exceeds the cache streams them from memory in every pass.
+// Replicas of similar contour length go together, and the groups are dealt to
+// the lanes by work, the largest first.
+void batch_split(pft_batch* b)
+{
+    std::vector<BatchGroup> cut;
+    for (BatchGroup& g : b->groups) {
+        std::stable_sort(g.reps.begin(), g.reps.end(), [&](int x, int y) { return b->ctx[x]->K > b->ctx[y]->K; });
+        double bytes = 0;
+        for (int r : g.reps) {
+            const pft_ctx* c = b->ctx[r];
+            bytes += (double)c->M * c->elem * (2 * g.ndir + (c->p.model == PFT_EDWARDS ? 1 : 2));
+        }
+        const size_t R = g.reps.size();
+        const size_t parts = std::min<size_t>(R, std::max<size_t>(1, (size_t)std::ceil(bytes / kGroupBytes)));
+        for (size_t i = 0; i < parts; ++i) {
+            BatchGroup h = g;
+            h.reps.assign(g.reps.begin() + R * i / parts, g.reps.begin() + R * (i + 1) / parts);
+            h.maxK = b->ctx[h.reps[0]]->K;
+            cut.push_back(h);
+        }
+    }
+    std::vector<double> work(cut.size(), 0.0);
+    std::vector<size_t> order(cut.size());
+    for (size_t i = 0; i < cut.size(); ++i) {
+        order[i] = i;
+        for (int r : cut[i].reps) work[i] += (double)b->ctx[r]->M * b->ctx[r]->K;
+    }
+    std::stable_sort(order.begin(), order.end(), [&](size_t x, size_t y) { return work[x] > work[y]; });
+    double load[kLanes] = {};
+    for (size_t i : order) {
+        const int l = (int)(std::min_element(load, load + kLanes) - load);
+        cut[i].lane = l;
+        load[l] += work[i];
+    }
+    b->groups = std::move(cut);
 }
 
 // Argument tables of a group's passes on the matrix cores, for both sweeps and
@@ -426,17 +479,21 @@ pft_status batch_enqueue_group(pft_batch* b, BatchGroup& g, int slot, bool updat
     return PFT_OK;
 }
 
-// Fork the group streams off the batch stream, enqueue every group, join.
+// Fork the lanes off the batch stream, enqueue every group on its lane, join.
 template <typename T>
 pft_status batch_enqueue(pft_batch* b, int slot, bool update, bool sis, const double2* logbuf, int64_t cap)
 {
     PFT_BHIP(b, hipEventRecord(b->fork, b->own));
-    for (BatchGroup& g : b->groups) {
-        PFT_BHIP(b, hipStreamWaitEvent(g.s, b->fork, 0));
-        pft_status st = batch_enqueue_group<T>(b, g, slot, update, sis);
-        if (st) return st;
-        PFT_BHIP(b, hipEventRecord(g.done, g.s));
-        PFT_BHIP(b, hipStreamWaitEvent(b->own, g.done, 0));
+    const int lanes = std::min<int>(kLanes, (int)b->groups.size());
+    for (int l = 0; l < lanes; ++l) {
+        PFT_BHIP(b, hipStreamWaitEvent(b->lane[l], b->fork, 0));
+        for (BatchGroup& g : b->groups) {
+            if (g.lane != l) continue;
+            pft_status st = batch_enqueue_group<T>(b, g, slot, update, sis);
+            if (st) return st;
+        }
+        PFT_BHIP(b, hipEventRecord(b->done[l], b->lane[l]));
+        PFT_BHIP(b, hipStreamWaitEvent(b->own, b->done[l], 0));
     }
     if (update) {
         if (logbuf)
@@ -464,7 +521,8 @@ pft_status batch_setup_t(pft_batch* b)
 pft_status batch_quiesce(pft_batch* b)
 {
     PFT_BHIP(b, hipStreamSynchronize(b->own));
-    for (BatchGroup& g : b->groups) PFT_BHIP(b, hipStreamSynchronize(g.s));
+    for (hipStream_t l : b->lane)
+        if (l) PFT_BHIP(b, hipStreamSynchronize(l));
     return PFT_OK;
 }
 
@@ -637,15 +695,12 @@ pft_status pft_batch_create(const pft_params* params, int32_t n, void* hip_strea
         g->maxK = std::max(g->maxK, b->ctx[r]->K);
         g->maxM = std::max<int64_t>(g->maxM, b->ctx[r]->M);
     }
-    if (s == PFT_OK) {
-        for (BatchGroup& g : b->groups) {
-            if (hipStreamCreateWithFlags(&g.s, hipStreamNonBlocking) != hipSuccess ||
-                hipEventCreateWithFlags(&g.done, hipEventDisableTiming) != hipSuccess) {
-                s = PFT_E_DEVICE;
-                break;
-            }
-        }
-    }
+    if (s == PFT_OK) batch_split(b);
+    for (int l = 0; l < kLanes && l < (int)b->groups.size() && s == PFT_OK; ++l)
+        if (hipStreamCreateWithFlags(&b->lane[l], hipStreamNonBlocking) != hipSuccess ||
+            hipEventCreateWithFlags(&b->done[l], hipEventDisableTiming) != hipSuccess)
+            s = PFT_E_DEVICE;
+    for (BatchGroup& g : b->groups) g.s = b->lane[g.lane];
     if (s == PFT_OK && (hipEventCreateWithFlags(&b->fork, hipEventDisableTiming) != hipSuccess ||
                         hipEventCreateWithFlags(&b->in, hipEventDisableTiming) != hipSuccess ||
                         hipEventCreateWithFlags(&b->out, hipEventDisableTiming) != hipSuccess ||
@@ -669,7 +724,8 @@ void pft_batch_destroy(pft_batch* b)
     if (!b) return;
     (void)hipStreamSynchronize(b->stream);
     if (b->own) (void)hipStreamSynchronize(b->own);
-    for (BatchGroup& g : b->groups) (void)hipStreamSynchronize(g.s);
+    for (hipStream_t l : b->lane)
+        if (l) (void)hipStreamSynchronize(l);
     batch_free(b);
     delete b;
 }
