@@ -18,6 +18,7 @@ BUILD = os.path.join(HERE, "_build")
 SOURCES = ["context.hip", "adjoint.hip", "batch.hip", "tune.hip", "static_step.hip",
            "passes_f64.hip", "passes_f32.hip", "passes_f64_alt.hip", "passes_f32_alt.hip",
            "planes_f64.hip", "planes_f32.hip", "mplanes_f64.hip", "mplanes_f32.hip", "maxis_f64.hip", "maxis_f32.hip",
+           "mpair_f64.hip", "mpair_f32.hip",
            "sis.hip", "passes_walls_f64.hip", "passes_walls_f32.hip",
            "stress_f64.hip", "stress_f32.hip", "stress_walls_f64.hip", "stress_walls_f32.hip",
            "planes_walls_f32_z0.hip", "planes_walls_f32_z1.hip", "planes_walls_f32_z2.hip"]
@@ -45,7 +46,8 @@ KERNEL_FILES = {
     "axis": ["fft.h", "kernels.h", "passes.inc", "passes_f64.hip", "passes_f32.hip", "passes_f64_alt.hip",
              "passes_f32_alt.hip",
              "mfma.h", "mlines.h", "maxis.h", "maxis.inc", "maxis_f64.hip", "maxis_f32.hip"],
-    "yzpass": ["fft.h", "kernels.h", "mfma.h", "mlines.h", "mplanes.h", "mplanes.inc", "mplanes_f64.hip", "mplanes_f32.hip", "planes.h", "planes.inc", "planes_f64.hip", "planes_f32.hip",
+    "yzpass": ["fft.h", "kernels.h", "mfma.h", "mlines.h", "mplanes.h", "mplanes.inc", "mplanes_f64.hip", "mplanes_f32.hip",
+               "mpair.h", "mpair.inc", "mpair_f64.hip", "mpair_f32.hip", "planes.h", "planes.inc", "planes_f64.hip", "planes_f32.hip",
                "planes_walls.inc", "planes_walls_f32_z0.hip", "planes_walls_f32_z1.hip", "planes_walls_f32_z2.hip"],
     "density": ["fft.h", "density.h"],
 }

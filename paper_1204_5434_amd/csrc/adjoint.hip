@@ -42,7 +42,7 @@ pft_status adjoint_t(pft_ctx* c, const double* wp, const double* wm, int Kc, dou
     // saddle point dH/dw is what is left of cancelling terms, and the rounding of
     // the passes is 1e-5 of it.
     const MatrixOff keep(c, std::is_same<T, float>::value);
-    const bool planes = std::is_same<T, double>::value && c->mplane && c->m[0] && c->fused;
+    const bool planes = std::is_same<T, double>::value && c->m[0] && (use_pair(c) || (c->mplane && c->fused));
     auto ends = [&](int prev, int next, const cx<T>* qin, cx<T>* qout, const Work& w = Work(), cx<T>* hcap = nullptr) {
         return planes ? yzpass<T>(c, prev, next, qin, qout, w, hcap) : zpass<T>(c, prev, next, qin, qout, w, hcap);
     };

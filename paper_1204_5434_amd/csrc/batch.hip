@@ -32,6 +32,7 @@ struct BatchGroup {
     int sp_axis[3] = {0, 0, 0};
     int var[3] = {0, 0, 0};      // kernel variants (x, y, z) of the group's grid
     bool fused = false;          // fused yz-plane schedule: zd holds PArgs, sd the x passes only
+    bool pair = false;           // axis schedule whose z and y passes share a launch (two launches a step, too)
     bool mz = false;             // the z or yz pass runs on the matrix cores: zd holds MArgs
     bool ms[3] = {false, false, false};  // so does strided pass k: its arguments are in md
     int lane = 0;
@@ -258,7 +259,7 @@ pft_status batch_build_pass_tables(pft_batch* b, BatchGroup& g)
                         d.skip = 1;
                         continue;
                     }
-                    d = g.fused ? sa[1] : sa[k];  // fused: the x pass alone
+                    d = g.fused || g.pair ? sa[1] : sa[k];  // two launches a step: the x pass alone
                     d.U = wU;
                     d.V = wV;
                     const int axk = g.sp_axis[k];
@@ -420,6 +421,8 @@ pft_status batch_enqueue_group(pft_batch* b, BatchGroup& g, int slot, bool updat
     auto zlaunch = [&](int p) -> hipError_t {
         const size_t at = (size_t)p * DR;
         const pft::MArgs<T>* md = static_cast<const pft::MArgs<T>*>(g.zd) + at;
+        if (g.pair)
+            return pft::launch_mpair_batch<T>(g.ny, g.nz, g.bc[1] != 0, g.bc[2] != 0, g.nx, md, DR, s);
         if (g.mz && g.fused) return pft::launch_myz_batch<T>(g.ny, g.nx, md, DR, s);
         if (g.mz) return pft::launch_mz_batch<T>(g.nz, g.bc[2] != 0, (int)nlines, md, DR, s);
         if (g.fused) return pft::launch_yzpass_batch<T>(g.ny, g.nx, pd + at, DR, s);
@@ -679,7 +682,8 @@ pft_status pft_batch_create(const pft_params* params, int32_t n, void* hip_strea
             for (int a = 0; a < 3; ++a) g->bc[a] = p.bc[a];
             g->ndir = p.model == PFT_EDWARDS ? 1 : 2;
             g->fused = fused;
-            if (g->fused) {
+            g->pair = !fused && use_pair(b->ctx[r]);
+            if (g->fused || g->pair) {
                 g->npass = 1;  // the x pass; the y and z work runs in the yz pass
                 g->sp_axis[0] = 0;
             } else {

@@ -312,7 +312,7 @@ pft_status apply_step_t(pft_ctx* c, int j, const double* qin, double* qout)
                        reinterpret_cast<const double2*>(qin), w0, c->M);
     PFT_HIP(c, hipGetLastError());
     pft_status s;
-    if (c->fused) {
+    if (two_launches(c)) {
         s = yzpass<T>(c, -1, j, w0, nullptr);
         if (s) return s;
         s = xpass_step<T>(c, j);
@@ -579,6 +579,7 @@ pft_status create_ctx(const pft_params* params, void* hip_stream, bool dual, pft
         c->m[ax] = ax < 2 ? (dbl ? pft::mx_supported<double>(na, wall) : pft::mx_supported<float>(na, wall))
                           : (dbl ? pft::mz_supported<double>(na, wall) : pft::mz_supported<float>(na, wall));
     }
+    c->pair = c->together && !c->mplane && pft::pair_supported(p.ny, p.nz);
     // Long periodic z lines lose to the line transforms (z pass, us: complex float
     // 48 points 10.0 / 7.2, 80 points 14.1 / 13.8; complex double 64 points 11.2 /
     // 12.3, 80 points 17.2 / 17.2; between walls 80 points 15.7 / 19.6 and 16.0 /

@@ -18,6 +18,7 @@
 #include "../../include/pft.h"
 #include "kernels.h"
 #include "maxis.h"
+#include "mpair.h"
 #include "mplanes.h"
 #include "mtable.h"
 #include "ops.h"
@@ -55,6 +56,7 @@ struct pft_ctx {
     bool fused_conj_only = false;     // ... only the conjugate sweep (the forward one runs axis passes)
     bool mplane = false;              // the fused pass runs on the matrix cores
     bool m[3] = {false, false, false};  // ... and so does this axis's own pass (x, y, z)
+    bool pair = false;                // axis schedule: z and y passes in one launch per plane (matrix cores)
     bool together = false;            // both sweeps advance in the same launches (small grids)
     size_t elem = 0;                  // bytes per propagator value
     // device buffers
@@ -414,6 +416,20 @@ pft_status zpass(pft_ctx* c, int prev, int next, const cx<T>* qin, cx<T>* qout, 
     return PFT_OK;
 }
 
+// Whether the axis schedule's z and y passes share a launch, and whether a step
+// is two launches (that or the fused schedule).
+inline bool use_pair(const pft_ctx* c) { return !c->fused && c->pair && c->m[1] && c->m[2]; }
+inline bool two_launches(const pft_ctx* c) { return c->fused || use_pair(c); }
+
+// The yz pass on the matrix cores.
+template <typename T>
+hipError_t launch_plane(const pft_ctx* c, const pft::MArgs<T>& a0, const pft::MArgs<T>& a1, int nsweeps, hipStream_t st)
+{
+    if (use_pair(c))
+        return pft::launch_mpair<T>(c->p.ny, c->p.nz, c->p.bc[1] != 0, c->p.bc[2] != 0, a0, a1, nsweeps, st);
+    return pft::launch_myz<T>(c->p.ny, a0, a1, nsweeps, st);
+}
+
 // Fused yz-plane pass completing step `prev` (-1: none: its Y2 and Z) and
 // starting step `next` (-1: none: its Z and Y1).
 template <typename T>
@@ -422,9 +438,9 @@ pft_status yzpass(pft_ctx* c, int prev, int next, const cx<T>* qin, cx<T>* qout,
 {
     hipStream_t st = w.stream ? w.stream : c->stream;
     ProfScope ps(c, PFT_K_YZPASS, zbytes(c, prev, next, qin, qout, hcap), st, true);
-    if (c->mplane) {
+    if (use_pair(c) || c->mplane) {
         const pft::MArgs<T> m = margs<T>(c, prev, next, qin, qout, w, hcap);
-        PFT_HIP(c, pft::launch_myz<T>(c->p.ny, m, m, 1, st));
+        PFT_HIP(c, launch_plane<T>(c, m, m, 1, st));
         return PFT_OK;
     }
     pft::PArgs<T> a = pargs<T>(c, prev, next, qin, qout);
@@ -506,25 +522,24 @@ template <typename T, class Out, class After>
 pft_status sweep_nodes(pft_ctx* c, bool backward, const Work& w, const Out& out, const After& after)
 {
     auto stepj = [&](int i) { return backward ? c->K - 1 - i : i; };
-    const bool fused = c->fused && (backward || !c->fused_conj_only);
-    pft_status s = fused ? yzpass<T>(c, -1, stepj(0), nullptr, out(0), w) : zpass<T>(c, -1, stepj(0), nullptr, out(0), w);
-    if (s) return s;
-    if ((s = after(0))) return s;
-    for (int i = 0; i < c->K; ++i) {
-        const int j = stepj(i);
-        const int next = i + 1 < c->K ? stepj(i + 1) : -1;
-        if (fused) {
-            // two passes per step: X, then yz completing it and starting the next
-            s = xpass_step<T>(c, j, w);
-            if (s) return s;
-            s = yzpass<T>(c, j, next, nullptr, out(i + 1), w);
-        } else {
-            s = step_body<T>(c, j, w);
-            if (s) return s;
-            s = zpass<T>(c, j, next, nullptr, out(i + 1), w);
-        }
+    const bool fused = use_pair(c) || (c->fused && (backward || !c->fused_conj_only));
+    const bool rqm4 = c->p.scheme == PFT_RQM4;
+    // completes step i - 1 and starts step i, up to the next x pass
+    auto ends = [&](int i) -> pft_status {
+        const int prev = i > 0 ? stepj(i - 1) : -1, next = i < c->K ? stepj(i) : -1;
+        cx<T>* const q = out(i);
+        if (fused) return yzpass<T>(c, prev, next, nullptr, q, w);
+        pft_status s = PFT_OK;
+        if (prev >= 0 && rqm4) s = ypass_step<T>(c, prev, true, false, w);
+        if (!s) s = zpass<T>(c, prev, next, nullptr, q, w);
+        if (!s && next >= 0) s = ypass_step<T>(c, next, rqm4, true, w);
+        return s;
+    };
+    for (int i = 0; i <= c->K; ++i) {
+        pft_status s = i > 0 ? xpass_step<T>(c, stepj(i - 1), w) : PFT_OK;
+        if (!s) s = ends(i);
+        if (!s) s = after(i);
         if (s) return s;
-        if ((s = after(i + 1))) return s;
     }
     return PFT_OK;
 }
@@ -538,13 +553,14 @@ pft_status sweep(pft_ctx* c, bool backward, void* store, const Work& w = Work())
 }
 
 // Whether every pass of the current schedule runs on the matrix cores.
-inline bool all_matrix(const pft_ctx* c) { return c->fused ? c->mplane && c->m[0] : c->m[0] && c->m[1] && c->m[2]; }
+inline bool all_matrix(const pft_ctx* c) { return c->m[0] && (c->fused ? c->mplane : c->m[1] && c->m[2]); }
 
 // Both sweeps in the same launches, each on its own work pair (all_matrix).
 template <typename T>
 pft_status sweeps_together(pft_ctx* c)
 {
     const int K = c->K;
+    const bool planes = two_launches(c);
     const bool rqm4 = c->p.scheme == PFT_RQM4;
     const double E = (double)c->elem * (double)c->M;
     const Work wb{c->U2, c->V2, nullptr};
@@ -553,10 +569,10 @@ pft_status sweeps_together(pft_ctx* c)
         const int b0 = i > 0 ? K - i : -1, b1 = i < K ? K - 1 - i : -1;
         const pft::MArgs<T> m0 = margs<T>(c, f0, f1, nullptr, slice<T>(c->qs, c, i));
         const pft::MArgs<T> m1 = margs<T>(c, b0, b1, nullptr, slice<T>(c->qds, c, i), wb);
-        ProfScope ps(c, c->fused ? PFT_K_YZPASS : PFT_K_ZPASS,
+        ProfScope ps(c, planes ? PFT_K_YZPASS : PFT_K_ZPASS,
                      zbytes(c, f0, f1, false, true, false) + zbytes(c, b0, b1, false, true, false), nullptr, true);
-        PFT_HIP(c, c->fused ? pft::launch_myz<T>(c->p.ny, m0, m1, 2, c->stream)
-                            : pft::launch_mz<T>(c->p.nz, c->p.bc[2] != 0, m0, m1, 2, c->stream));
+        PFT_HIP(c, planes ? launch_plane<T>(c, m0, m1, 2, c->stream)
+                          : pft::launch_mz<T>(c->p.nz, c->p.bc[2] != 0, m0, m1, 2, c->stream));
         return PFT_OK;
     };
     auto y = [&](int i, bool onV) -> pft_status {
@@ -567,12 +583,12 @@ pft_status sweeps_together(pft_ctx* c)
     };
     pft_status s = ends(0);
     for (int i = 0; i < K && !s; ++i) {
-        if (!c->fused && (s = y(i, true))) return s;
+        if (!planes && (s = y(i, true))) return s;
         {
             ProfScope ps(c, PFT_K_XPASS, 2 * xbytes(c, false, false), nullptr, true);
             PFT_HIP(c, pft::launch_mx<T>(c->p.nx, c->p.bc[0] != 0, mxargs<T>(c, i), mxargs<T>(c, K - 1 - i, wb), 2, c->stream));
         }
-        if (!c->fused && rqm4 && (s = y(i, false))) return s;
+        if (!planes && rqm4 && (s = y(i, false))) return s;
         s = ends(i + 1);
     }
     return s;

@@ -77,6 +77,30 @@ def test_uneven_grids_and_walls(orc, n, bc, scheme, prec):
     assert abs(got["Q"][0] - ref["Q"]) <= tq * abs(ref["Q"])
 
 
+# lengths that meet in one yz launch: rows and columns of one strip and of several,
+# the remainder of a strip, the largest pair that fits, walls on either axis
+PAIRS = [((8, 40, 24), (0, 0, 0)), ((8, 24, 40), (0, 1, 0)), ((8, 48, 40), (0, 0, 2)), ((8, 40, 48), (0, 2, 1)),
+         ((8, 8, 48), (0, 0, 1)), ((8, 12, 8), (0, 0, 0)), ((8, 32, 32), (0, 1, 1)), ((8, 20, 48), (0, 0, 0))]
+
+
+@pytest.mark.parametrize("prec", [B.PFT_C128, B.PFT_C64])
+@pytest.mark.parametrize("n,bc", PAIRS, ids=[f"{n}-{bc}" for n, bc in PAIRS])
+def test_yz_pass_of_uneven_planes(n, bc, prec):
+    r = np.random.default_rng(sum(n))
+    wp, wm = (torch.from_numpy(0.4 * r.standard_normal(n) + 0.1j * r.standard_normal(n)).to(DEV) for _ in range(2))
+    ctx = B.Context(B.Params(*n, *[0.12 * a for a in n], 7, 0.4, 15.0, 2.0, prec, 0, B.PFT_DIBLOCK, 0.0, 0, bc))
+    got = evaluate(ctx, wp, wm)
+    ctx.pft_set_concurrent_sweeps(False)
+    alone = evaluate(ctx, wp, wm)
+    ctx.pft_set_variant(1, 0)  # z and y passes apart, y by line transforms
+    apart = evaluate(ctx, wp, wm)
+    ctx.close()
+    tol = 1e-10 if prec == B.PFT_C128 else 2e-5
+    for key in ("phiA", "phiB", "Q"):
+        assert np.array_equal(got[key], alone[key]), key
+        assert np.abs(got[key] - apart[key]).max() <= tol * np.abs(apart[key]).max(), key
+
+
 @pytest.mark.parametrize("prec", [B.PFT_C128, B.PFT_C64])
 def test_constant_and_nonfinite_fields(prec):
     """A uniform field leaves q uniform (its closed form, Eq. (5)); a field
