@@ -219,6 +219,7 @@ struct Work {
     void* U = nullptr;
     void* V = nullptr;
     hipStream_t stream = nullptr;  // NULL: the context's stream
+    int x0 = 0, nx = 0;            // z and y passes: planes x0 .. x0 + nx - 1 only (nx = 0: all)
 };
 
 // The z pass on the context's grid (the walled kernels on a walled z axis).
@@ -245,6 +246,8 @@ pft_status spass(pft_ctx* c, int axis, pft::SOps<T> opU, pft::SOps<T> opV, const
     if (opU.g1 && opU.e) bytes += E;
     if (opV.g1 && opV.e && !(opU.g1 && opU.e == opV.e)) bytes += E;
     hipStream_t st = w.stream ? w.stream : c->stream;
+    const int planes = w.nx ? w.nx : c->p.nx;  // of a y pass
+    if (axis == 1) bytes = bytes * planes / c->p.nx;
     ProfScope ps(c, axis == 0 ? PFT_K_XPASS : PFT_K_YPASS, bytes, st, c->p.bc[axis] == 0);
     const int64_t nynz = (int64_t)c->p.ny * c->p.nz;
     if (axis == 0) {
@@ -257,10 +260,12 @@ pft_status spass(pft_ctx* c, int axis, pft::SOps<T> opU, pft::SOps<T> opV, const
     } else {
         a.S = c->p.nz;
         a.slab_stride = nynz;
+        a.U += w.x0 * nynz;
+        a.V += w.x0 * nynz;
         if (c->p.bc[1])
-            PFT_HIP(c, pft::launch_spass_walls<T>(1, c->p.ny, c->p.bc[1], c->p.nz, a, c->p.nx, st));
+            PFT_HIP(c, pft::launch_spass_walls<T>(1, c->p.ny, c->p.bc[1], c->p.nz, a, planes, st));
         else
-            PFT_HIP(c, pft::launch_spass<T>(1, c->p.ny, c->var[1], c->p.nz, a, c->p.nx, st));
+            PFT_HIP(c, pft::launch_spass<T>(1, c->p.ny, c->var[1], c->p.nz, a, planes, st));
     }
     return PFT_OK;
 }
@@ -402,9 +407,22 @@ pft_status zpass(pft_ctx* c, int prev, int next, const cx<T>* qin, cx<T>* qout, 
                  cx<T>* hcap = nullptr)
 {
     hipStream_t st = w.stream ? w.stream : c->stream;
-    ProfScope ps(c, PFT_K_ZPASS, zbytes(c, prev, next, qin, qout, hcap), st, c->m[2] || c->p.bc[2] == 0);
+    const int planes = w.nx ? w.nx : c->p.nx;
+    ProfScope ps(c, PFT_K_ZPASS, zbytes(c, prev, next, qin, qout, hcap) * planes / c->p.nx, st, c->m[2] || c->p.bc[2] == 0);
+    const int64_t off = (int64_t)w.x0 * c->p.ny * c->p.nz;
+    auto part = [&](auto& a) {  // the arguments of the planes asked for
+        a.nlines = planes * c->p.ny;
+        a.U += off;
+        a.V += off;
+        if (a.qin) a.qin += off;
+        if (a.qout) a.qout += off;
+        if (a.hcap) a.hcap += off;
+        if (a.Ep) a.Ep += off;
+        if (a.En) a.En += off;
+    };
     if (c->m[2]) {
-        const pft::MArgs<T> m = margs<T>(c, prev, next, qin, qout, w, hcap);
+        pft::MArgs<T> m = margs<T>(c, prev, next, qin, qout, w, hcap);
+        part(m);
         PFT_HIP(c, pft::launch_mz<T>(c->p.nz, c->p.bc[2] != 0, m, m, 1, st));
         return PFT_OK;
     }
@@ -412,6 +430,7 @@ pft_status zpass(pft_ctx* c, int prev, int next, const cx<T>* qin, cx<T>* qout, 
     if (w.U) a.U = static_cast<cx<T>*>(w.U);
     if (w.V) a.V = static_cast<cx<T>*>(w.V);
     a.hcap = hcap;
+    part(a);
     PFT_HIP(c, launch_z<T>(c, a, st));
     return PFT_OK;
 }
@@ -491,8 +510,12 @@ pft_status ypass_step(pft_ctx* c, int j, bool onU, bool onV, const Work& w = Wor
     const int hd = c->hid[j];
     if (c->m[1]) {
         hipStream_t st = w.stream ? w.stream : c->stream;
-        const pft::MXArgs<T> m = myargs<T>(c, j, onU, onV, w);
-        ProfScope ps(c, PFT_K_YPASS, 2.0 * (onU + onV) * (double)c->elem * (double)c->M, st, true);
+        pft::MXArgs<T> m = myargs<T>(c, j, onU, onV, w);
+        const int planes = w.nx ? w.nx : c->p.nx;
+        m.ncols = planes * c->p.nz;
+        if (m.U) m.U += w.x0 * m.slab_stride;
+        if (m.V) m.V += w.x0 * m.slab_stride;
+        ProfScope ps(c, PFT_K_YPASS, 2.0 * (onU + onV) * (double)c->elem * (double)c->M * planes / c->p.nx, st, true);
         PFT_HIP(c, pft::launch_mx<T>(c->p.ny, c->p.bc[1] != 0, m, m, 1, st));
         return PFT_OK;
     }
@@ -515,6 +538,23 @@ pft_status step_body(pft_ctx* c, int j, const Work& w = Work(), cx<T>* capA = nu
     return ypass_step<T>(c, j, true, false, w);
 }
 
+// Planes per slab of the axis schedule's z and y passes.  Between two x passes
+// these stay inside one x-plane.  Where the arrays exceed the Infinity Cache they
+// run slab by slab, so that what one pass writes of a slab is still there when
+// the next reads it (us per contour step, both sweeps: 256^3 complex double 1879
+// whole, 1755 in slabs of 64 MiB, 1791 of 32, 1833 of 24, 2008 of 16, whose
+// launches no longer fill the device; complex float 894 / 861 / 882 / 893 / 927;
+// a smaller array gains nothing: 256 x 128 x 128 complex double, one of 64 MiB,
+// 415 whole, 427 in two).
+inline int slab_planes(const pft_ctx* c)
+{
+    constexpr double kSlab = 64.0 * (1 << 20);
+    const double array = (double)c->M * (double)c->elem;
+    if (array < 2 * kSlab) return c->p.nx;
+    const int parts = std::min(c->p.nx, (int)std::ceil(array / kSlab));
+    return (c->p.nx + parts - 1) / parts;
+}
+
 // One sweep over the K steps, forward (q) or mirrored (q-dagger).  Node i
 // (i = 0..K, in sweep order) is written to out(i), and after(i) runs once the
 // pass that stores it has been enqueued.
@@ -524,16 +564,22 @@ pft_status sweep_nodes(pft_ctx* c, bool backward, const Work& w, const Out& out,
     auto stepj = [&](int i) { return backward ? c->K - 1 - i : i; };
     const bool fused = use_pair(c) || (c->fused && (backward || !c->fused_conj_only));
     const bool rqm4 = c->p.scheme == PFT_RQM4;
+    const int slab = slab_planes(c);
     // completes step i - 1 and starts step i, up to the next x pass
     auto ends = [&](int i) -> pft_status {
         const int prev = i > 0 ? stepj(i - 1) : -1, next = i < c->K ? stepj(i) : -1;
         cx<T>* const q = out(i);
         if (fused) return yzpass<T>(c, prev, next, nullptr, q, w);
-        pft_status s = PFT_OK;
-        if (prev >= 0 && rqm4) s = ypass_step<T>(c, prev, true, false, w);
-        if (!s) s = zpass<T>(c, prev, next, nullptr, q, w);
-        if (!s && next >= 0) s = ypass_step<T>(c, next, rqm4, true, w);
-        return s;
+        Work part = w;
+        for (part.x0 = 0; part.x0 < c->p.nx; part.x0 += slab) {
+            part.nx = std::min(slab, c->p.nx - part.x0);
+            pft_status s = PFT_OK;
+            if (prev >= 0 && rqm4) s = ypass_step<T>(c, prev, true, false, part);
+            if (!s) s = zpass<T>(c, prev, next, nullptr, q, part);
+            if (!s && next >= 0) s = ypass_step<T>(c, next, rqm4, true, part);
+            if (s) return s;
+        }
+        return PFT_OK;
     };
     for (int i = 0; i <= c->K; ++i) {
         pft_status s = i > 0 ? xpass_step<T>(c, stepj(i - 1), w) : PFT_OK;

@@ -11,16 +11,32 @@ namespace pft::rt {
 
 // Kernel variant per (precision, axis length, kind: 0 = z pass, 1 = x pass,
 // 2 = y pass), used by contexts created afterwards; filled by pft_autotune or
-// pft_tune_load (also from $PFT_TUNE_CACHE on the first pft_create).
+// pft_tune_load (also from $PFT_TUNE_CACHE on the first pft_create); -1: neither.
 namespace {
-int g_tune[2][257][3] = {};
+struct Tune {
+    int v[2][257][3];
+    Tune() { std::memset(v, -1, sizeof v); }
+} g_tuned;
+auto& g_tune = g_tuned.v;
 std::once_flag g_tune_env;
+
+// Without either: lines of 128 points on kernels bounded to two waves per SIMD
+// (cube, both sweeps on two streams: complex double 200.8 -> 190.5 us per contour
+// step, complex float 111.3 -> 107.9), and the x and y passes of 256 points in
+// complex double on the wide tile (1888 -> 1841 us).
+int default_variant(int prec, int n, int kind)
+{
+    if (n == 128) return 2;
+    if (n == 256 && prec == PFT_C128 && kind > 0) return 1;
+    return 0;
+}
 }  // namespace
 
 int tuned_variant(int prec, int n, int kind)
 {
     int n1, n2, w;
-    const int v = (n >= 0 && n <= 256) ? g_tune[prec & 1][n][kind] : 0;
+    int v = (n >= 0 && n <= 256) ? g_tune[prec & 1][n][kind] : 0;
+    if (v < 0) v = default_variant(prec & 1, n, kind);
     return pft::axis_variant(n, v, &n1, &n2, &w) ? v : 0;
 }
 
@@ -189,7 +205,7 @@ pft_status pft_tune_save(const char* path)
         for (int n = 0; n <= 256; ++n)
             for (int kind = 0; kind < 3; ++kind)
                 if (pft::axis_supported(n))
-                    std::fprintf(f, "%s %d %d %d %d\n", arch.c_str(), prec, n, kind, g_tune[prec][n][kind]);
+                    std::fprintf(f, "%s %d %d %d %d\n", arch.c_str(), prec, n, kind, tuned_variant(prec, n, kind));
     std::fclose(f);
     return PFT_OK;
 }
