@@ -10,10 +10,19 @@
 // u_B = E4 lambda, u_A = E2 A_lambda, u_C = E2 lambda (E2 = E4^2).  Each
 // kernel applies -d^2/dx_a^2 to the captures along its own lines (forward
 // transform, multiply by (2 pi m / L_a)^2 / N_a, inverse) and dots the result
-// with the partners at once, so no derivative array is ever written.  Each
-// capture has its own row of workgroups (blockIdx.y); every workgroup adds its
-// FP64 sum to a partial slot of its own, summed over the steps and reduced
-// once at the end.
+// with the partners at once, so no derivative array is ever written.  Every
+// workgroup adds its FP64 sum to a partial slot of its own, summed over the steps
+// and reduced once at the end.
+//
+// Each capture of a tile of lines is a workgroup of its own, for the number of
+// wavefronts in flight.  The three of a tile share E4 and lambda: they are
+// numbered so that they follow each other on one XCD (workgroups go round the
+// XCDs in order) and find those in its L2 (96^3 complex double, a strided pass
+// beside the recomputation's: 28.7 us with all workgroups of a capture in a row,
+// 27.1 us so).  What bounds it is the chain of loads, transform and loads; E4 and
+// lambda requested before the transform cost more registers than they hide
+// (gradient 40.2 -> 40.8 ms), and so did the accumulation of dH/dw as a fourth
+// workgroup of the z pass (46.7 ms).
 // Along a walled axis (EXT = 1 reflecting, 2 absorbing) the modes are
 // k = pi m / L_a, which scale with 1/L_a as well, so the same sum holds with
 // -d^2/dx_a^2 taken in the cosine / sine basis: the line is loaded in the
@@ -35,6 +44,8 @@ struct StressPass {
     const cx<T>* lam;   // lambda_{j+1}
     const cx<T>* Alam;  // the adjoint-side capture A (Richardson step only)
     const cx<T>* E4;    // the step's E4 table
+    int ntile;          // workgroups per capture
+    int rows;           // captures present
     const T* d2;        // (2 pi m / L_a)^2 / N_a in natural order; walled: the pair
                         // factors (alpha, beta re, beta im) per m of (pi m / L_a)^2 / N_a
     int64_t nlines;     // z pass: lines of nz contiguous points
@@ -42,6 +53,18 @@ struct StressPass {
     int64_t slab_stride;
     int ncols, ntiles;
     double2* part;      // one slot per workgroup, accumulated
+};
+
+// Tile and row of this workgroup: the rows of a tile are kXcds apart.
+constexpr int kXcds = 8;
+struct StressTile {
+    int tile, row;
+    __device__ __forceinline__ explicit StressTile(int rows)
+    {
+        const int group = (int)blockIdx.x / kXcds;
+        row = group % rows;
+        tile = group / rows * kXcds + (int)blockIdx.x % kXcds;
+    }
 };
 
 // Compensated FP64 sum (Neumaier).
@@ -106,11 +129,13 @@ __global__ __launch_bounds__((ZShape<N1, N2, 1>::kThreads)) void k_stress_z(Stre
     constexpr int N = N1 * N2;
     constexpr int LPW = ZShape<N1, N2, 1>::kLines;
     const int t = threadIdx.x % N2, l = threadIdx.x / N2;
-    const int64_t line = (int64_t)blockIdx.x * LPW + l;
+    const StressTile b(A.rows);
+    if (b.tile >= A.ntile) return;
+    const int64_t line = (int64_t)b.tile * LPW + l;
     const bool act = line < A.nlines;
     auto pos = [&](int r) { return line * N + ext_index<EXT, N>(r * N2 + t); };
     const LayZ<N1, N2> lay{l};
-    const int i = A.first + (int)blockIdx.y;  // one capture per workgroup row
+    const int i = A.first + b.row;
     CSum re, im;
     cx<T> a[N1];
     sfor<0, N1>([&](auto I) {
@@ -128,7 +153,7 @@ __global__ __launch_bounds__((ZShape<N1, N2, 1>::kThreads)) void k_stress_z(Stre
     }
     const double2 s = stress_block_sum(make_double2(re.value(), im.value()), red, ZShape<N1, N2, 1>::kThreads);
     if (threadIdx.x == 0) {
-        const int64_t k = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+        const int64_t k = (int64_t)b.row * A.ntile + b.tile;
         const double2 o = A.part[k];
         A.part[k] = make_double2(o.x + s.x, o.y + s.y);
     }
@@ -145,13 +170,15 @@ __global__ __launch_bounds__((SShape<T, N2, 1>::kThreads)) void k_stress_s(Stres
     __shared__ double2 red[NT];
     cx<T>* sh = reinterpret_cast<cx<T>*>(smem_raw);
     const int c = threadIdx.x % TC, t = threadIdx.x / TC;
-    const int slab = blockIdx.x / A.ntiles, tile = blockIdx.x % A.ntiles;
+    const StressTile b(A.rows);
+    if (b.tile >= A.ntile) return;
+    const int slab = b.tile / A.ntiles, tile = b.tile % A.ntiles;
     const int col = tile * TC + c;
     const bool act = col < A.ncols;
     const int64_t base = (int64_t)slab * A.slab_stride + col;
     auto pos = [&](int r) { return base + (int64_t)ext_index<EXT, N>(r * N2 + t) * A.S; };
     const LayS<N2, TC> lay{c};
-    const int i = A.first + (int)blockIdx.y;  // one capture per workgroup row
+    const int i = A.first + b.row;
     CSum re, im;
     cx<T> a[N1];
     sfor<0, N1>([&](auto I) {
@@ -169,7 +196,7 @@ __global__ __launch_bounds__((SShape<T, N2, 1>::kThreads)) void k_stress_s(Stres
     }
     const double2 s = stress_block_sum(make_double2(re.value(), im.value()), red, NT);
     if (threadIdx.x == 0) {
-        const int64_t k = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+        const int64_t k = (int64_t)b.row * A.ntile + b.tile;
         const double2 o = A.part[k];
         A.part[k] = make_double2(o.x + s.x, o.y + s.y);
     }
