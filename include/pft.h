@@ -153,8 +153,10 @@ pft_status pft_create(const pft_params* params, void* hip_stream, pft_ctx** out)
  * pft_propagate runs on a second (default-priority) stream with its own work
  * arrays, forked from and joined back to the context stream, so the memory
  * phases of one overlap the on-chip transform phases of the other (and
- * pft_adjoint recomputes its next segment there).  on = 0 runs everything on
- * the context stream.  Errors: PFT_E_INVALID. */
+ * pft_adjoint recomputes its next segment there).  On small grids (arrays below
+ * 4 MiB) whose passes all run on the matrix cores, both sweeps advance in the
+ * same launches on the context stream instead.  on = 0 runs the sweeps one after
+ * the other on the context stream.  Errors: PFT_E_INVALID. */
 pft_status pft_set_concurrent_sweeps(pft_ctx* ctx, int32_t on);
 
 /* Schedule of the sweeps (Eq. (12) either way; results agree to rounding).
@@ -163,12 +165,18 @@ pft_status pft_set_concurrent_sweeps(pft_ctx* ctx, int32_t on);
  * float: up to 128 x 128; complex double: up to 96 x 96) the y, z, y passes
  * between two x passes fuse into one pass per x-plane, and a step moves 11
  * instead of 17 arrays.  New contexts use the fused schedule where it exists
- * and its compiled kernel spills at most 256 bytes per lane (on gfx950 every
- * such plane except complex double 96 x 96, measured slower than the axis
- * schedule); pft_set_fused_planes overrides the choice.
+ * and was measured faster: square periodic planes up to 64 x 64 on the matrix
+ * cores, larger ones and walled ones where the kernel compiled for the line
+ * transforms spills at most 256 bytes per lane (on gfx950 every such plane
+ * except complex double 96 x 96) and the axis passes don't run on the matrix
+ * cores between walls; pft_set_fused_planes overrides the choice.
+ * The axis schedule of a small grid whose planes are not square, or have walls,
+ * runs its y, z, y passes in one launch where the plane's two lengths are at most
+ * 48 and two copies of it fit in 64 KB.
  * The schedule applies to pft_propagate, pft_cl_step and pft_apply_step, and
  * batches use the fused one for every replica group whose shape has it; the
- * reverse mode (pft_adjoint) always uses the axis schedule.
+ * reverse mode (pft_adjoint) uses fused passes in complex double where they run
+ * on the matrix cores, and the axis schedule otherwise.
  * on = 2 fuses only the conjugate (q-dagger) sweep of pft_propagate, whose
  * on-chip-bound plane passes then share the device with the forward sweep's
  * memory-bound axis passes when the two sweeps run concurrently.
@@ -345,10 +353,11 @@ pft_status pft_noise_normals(uint64_t seed, uint64_t replica, uint64_t step, int
 /* ---- batches of independent replicas --------------------------------------
  * Many independent systems (SCFT candidates or complex-Langevin replicas,
  * each its own pft_params: grid, box, ns, f, chiN, C) advanced together.
- * Replicas with the same grid shape and walls form a group; every axis pass of a group
+ * Replicas with the same grid shape and walls form groups, cut where the arrays of
+ * one would outgrow the cache; every axis pass of a group
  * is one launch over all its replicas (per-replica arguments come from device
- * tables, uneven contour step counts are masked); groups run on their own
- * streams; one field step of the whole batch is captured in a HIP graph and
+ * tables, uneven contour step counts are masked); groups are dealt to four
+ * streams by work; one field step of the whole batch is captured in a HIP graph and
  * replayed.  All replicas must share precision, scheme and model (Edwards
  * replicas run one sweep each and take w_minus = NULL).  This fills the
  * GPU with small grids, which on their own cannot hide memory latency
@@ -400,6 +409,8 @@ pft_status pft_batch_sync(pft_batch* batch);
  * axis; the z pass completing and starting a Richardson step, the x pass on
  * both arrays with its field multiply, the y pass on both arrays) and makes
  * the fastest of each the default for contexts and batches created afterwards.
+ * Variants are those of the line transforms: passes that run on the matrix cores
+ * (short axes) have one form and don't use them.
  * choices (may be NULL): 3 ints per size (z, x, y variant);
  * timings (may be NULL): 3 * PFT_MAX_VARIANTS doubles per size (ms per launch,
  * z then x then y, variants 0.., -1 where a variant does not exist).
@@ -414,7 +425,8 @@ pft_status pft_autotune(int32_t precision, const int32_t* sizes, int32_t nsizes,
 pft_status pft_tune_save(const char* path);
 pft_status pft_tune_load(const char* path);
 /* Force kernel variant `variant` on one axis (0 = x, 1 = y, 2 = z) of a
- * context (checking every variant against the oracle).  Errors:
+ * context (checking every variant against the oracle); an axis whose pass ran
+ * on the matrix cores runs it by line transforms from then on.  Errors:
  * PFT_E_INVALID, PFT_E_UNSUPPORTED (no such variant). */
 pft_status pft_set_variant(pft_ctx* ctx, int32_t axis, int32_t variant);
 
