@@ -169,7 +169,8 @@ pft_status pft_set_concurrent_sweeps(pft_ctx* ctx, int32_t on);
  * cores, larger ones and walled ones where the kernel compiled for the line
  * transforms spills at most 256 bytes per lane (on gfx950 every such plane
  * except complex double 96 x 96) and the axis passes don't run on the matrix
- * cores between walls; pft_set_fused_planes overrides the choice.
+ * cores between walls, and where the grid has planes enough for the larger ones;
+ * pft_set_fused_planes overrides the choice.
  * The axis schedule of a small grid whose planes are not square, or have walls,
  * runs its y, z, y passes in one launch where the plane's two lengths are at most
  * 48 and two copies of it fit in 64 KB.

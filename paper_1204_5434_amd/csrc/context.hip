@@ -533,6 +533,22 @@ static bool fused_default(const pft_params& p)
     return b >= 0 && b <= kFusedMaxSpill;
 }
 
+// Whether a periodic grid has too few planes for the line transforms' fused pass,
+// which gives each a workgroup (128 x 128: a compute unit), `sweeps` at a time.
+// us per contour step, fused / axis schedule: complex float 128 x 128, two sweeps
+// 16 planes 55.7 / 38.2, 64 planes 66.5 / 66.2, 96 planes 78.0 / 87.8; one sweep
+// 16 planes 49.1 / 28.5, 128 planes 66.3 / 61.3, 192 planes 79.3 / 84.7; 96 x 96, two
+// sweeps 32 planes 48.5 / 46.5, 64 planes 51.0 / 57.6, one 42.3 / 38.9 and 48.8 /
+// 49.8, 80 x 80 alike; complex double 80 x 80, two sweeps 32 planes 56.6 / 51.6, 64
+// planes 64.0 / 61.6, 96 planes 81.3 / 87.2, one 52.6 / 40.2, 58.4 / 52.2, 67.2 / 64.4
+// and with 128 planes 66.5 / 68.5.
+static bool few_planes(const pft_params& p, int sweeps)
+{
+    if (p.bc[1] || p.bc[2]) return false;
+    if (p.precision == PFT_C128) return p.nx * sweeps <= (sweeps == 2 ? 128 : 96);
+    return p.ny >= 128 ? p.nx * sweeps <= 128 : p.nx <= 32;
+}
+
 pft_status create_ctx(const pft_params* params, void* hip_stream, bool dual, pft_ctx** out)
 {
     if (!out) return PFT_E_INVALID;
@@ -551,7 +567,8 @@ pft_status create_ctx(const pft_params* params, void* hip_stream, bool dual, pft
         if (p.bc[a] && !pft::walls_supported(a == 0 ? p.nx : a == 1 ? p.ny : p.nz)) return PFT_E_UNSUPPORTED;
     }
     if (p.storage != PFT_STORE_BOTH && ed) return PFT_E_UNSUPPORTED;
-    if (ed || p.storage != PFT_STORE_BOTH) dual = false;  // one sweep, or sweeps in sequence
+    const bool alone = dual && (ed || p.storage != PFT_STORE_BOTH);  // one sweep, or sweeps in sequence
+    if (alone) dual = false;
     if (!pft::axis_supported(p.nx) || !pft::axis_supported(p.ny) || !pft::axis_supported(p.nz))
         return PFT_E_UNSUPPORTED;
 
@@ -586,7 +603,8 @@ pft_status create_ctx(const pft_params* params, void* hip_stream, bool dual, pft
     // 25.1), unless that lets a small grid share its launches.
     if (!p.bc[2] && !c->together && p.nz > (dbl ? 64 : 40)) c->m[2] = false;
     // between walls the axis passes on the matrix cores beat the line transforms' fused pass
-    c->fused = c->mplane || (!((p.bc[1] || p.bc[2]) && c->m[1] && c->m[2]) && fused_default(p));
+    c->fused = c->mplane || (!((p.bc[1] || p.bc[2]) && c->m[1] && c->m[2]) &&
+                             !((alone || dual) && few_planes(p, alone ? 1 : 2)) && fused_default(p));
     c->stream = static_cast<hipStream_t>(hip_stream);
     // table slot length: n factors per periodic axis, 3n per walled axis
     c->maxN = std::max((p.bc[0] ? 3 : 1) * p.nx, std::max((p.bc[1] ? 3 : 1) * p.ny, (p.bc[2] ? 3 : 1) * p.nz));
