@@ -581,9 +581,10 @@ pft_status create_ctx(const pft_params* params, void* hip_stream, bool dual, pft
         delete c;
         return PFT_E_DEVICE;
     }
-    c->var[0] = tuned_variant(p.precision, p.nx, 1);
-    c->var[1] = tuned_variant(p.precision, p.ny, 2);
-    c->var[2] = tuned_variant(p.precision, p.nz, 0);
+    const bool walls = p.bc[2] || (p.precision == PFT_C64 && p.bc[1]);
+    c->var[0] = tuned_variant(p.precision, p.nx, 1, walls);
+    c->var[1] = tuned_variant(p.precision, p.ny, 2, walls);
+    c->var[2] = tuned_variant(p.precision, p.nz, 0, walls);
     const bool dbl = p.precision == PFT_C128;
     c->mplane = p.ny == p.nz && !p.bc[1] && !p.bc[2] &&
                 (dbl ? pft::mplane_supported<double>(p.ny) : pft::mplane_supported<float>(p.ny));

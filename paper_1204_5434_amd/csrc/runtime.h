@@ -738,7 +738,8 @@ namespace pft::rt {
 int contour_plan(int ns, double f, double* h, int* blk, int* junction);
 // Kernel variant of an axis pass per (precision, axis length, kind: 0 = z
 // pass, 1 = x pass, 2 = y pass) for contexts created from now on (autotuner).
-int tuned_variant(int prec, int n, int kind);
+// walls: the grid has some that the untuned choice was not made for
+int tuned_variant(int prec, int n, int kind, bool walls = false);
 void tune_env_once();
 pft_status create_ctx(const pft_params* params, void* hip_stream, bool dual, pft_ctx** out);
 void free_all(pft_ctx* c);
