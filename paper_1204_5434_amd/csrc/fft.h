@@ -345,24 +345,34 @@ __device__ __forceinline__ void dft(cx<T>* v)
 // line to its LDS slot.  Every lane of the workgroup must call diffuse()
 // (it contains barriers); lanes without a line pass zeros.
 //
-// MEAN (diffusion factors, whose k = 0 entry is 1/N): in complex float the
-// k = 0 mode is divided by N in double and rounded once, instead of being
-// multiplied by 1/N rounded to float.  1/N is not a float for N with a factor
-// 3 or 5, and its rounding error would scale the mean of q by the same factor
-// in every pass of every contour step, an error that grows linearly with the
-// number of steps in Q.
+// MEAN (diffusion factors, whose k = 0 entry is 1/N): the k = 0 mode is divided
+// by N with one rounding, instead of being multiplied by the rounded 1/N.  1/N is
+// not a float or double for N with a factor 3 or 5, and its rounding error would
+// scale the mean of q by the same factor in every pass of every contour step, an
+// error that grows linearly with the number of steps in Q (complex double, a film
+// of 80 x 96 x 40 points whose y axis alone runs here, 76 steps, against 80-bit
+// arithmetic: Q off by 1.4e-14 with the rounded 1/96, 4e-15 without it).
+// Complex float divides in double; complex double adds what 1/N lost to rounding.
+constexpr bool power_of_two(int n) { return (n & (n - 1)) == 0; }
 template <int N, typename T>
 __device__ __forceinline__ cx<T> mean_over_n(cx<T> x)
 {
     constexpr double inv = 1.0 / N;
-    return {T(double(x.re) * inv), T(double(x.im) * inv)};
+    if constexpr (std::is_same<T, float>::value) {
+        return {T(double(x.re) * inv), T(double(x.im) * inv)};
+    } else {
+        // 1/N - inv, from products that are exact: N times each half of inv's digits
+        constexpr double up = inv * 134217729.0, head = up - (up - inv), tail = inv - head;
+        constexpr double rest = ((1.0 - N * head) - N * tail) / N;
+        return {__builtin_fma(x.re, inv, x.re * rest), __builtin_fma(x.im, inv, x.im * rest)};
+    }
 }
 
 template <int N1, int N2, bool MEAN = false, typename T, class Lay, class G>
 __device__ __forceinline__ void diffuse(cx<T> (&a)[N1], int t, cx<T>* __restrict__ sh, const Lay& lay, const G& g)
 {
     constexpr int N = N1 * N2;
-    constexpr bool kMean = MEAN && std::is_same<T, float>::value;
+    constexpr bool kMean = MEAN && (std::is_same<T, float>::value || !power_of_two(N));
     if constexpr (N2 == 1) {
         dft<N1, false>(a);
         sfor<0, N1>([&](auto K) {
@@ -421,13 +431,16 @@ __device__ __forceinline__ void diffuse(cx<T> (&a)[N1], int t, cx<T>* __restrict
 //   alpha_m = (g_m + g_{N-m}) / 2,  beta_m = (g_m - g_{N-m}) exp(i pi m / N) / 2
 // (alpha_0 = g_0, beta_0 = 0; absorbing walls use g_m of sine mode N - m).
 // ab holds (alpha_m, Re beta_m, Im beta_m) for m = 0..N-1 with 1/N folded in.
+// MEAN (reflecting walls, whose k = 0 mode is the mean: alpha_0 = 1/N) as in
+// diffuse().
 // The pairing of m with N - m crosses lanes, so the stage-two spectrum goes
 // through LDS once more than in diffuse(); same calling rules as diffuse().
-template <int N1, int N2, typename T, class Lay>
+template <int N1, int N2, bool MEAN = false, typename T, class Lay>
 __device__ __forceinline__ void pair_diffuse(cx<T> (&a)[N1], int t, cx<T>* __restrict__ sh, const Lay& lay,
                                              const T* __restrict__ ab)
 {
     constexpr int N = N1 * N2;
+    constexpr bool kMean = MEAN && !power_of_two(N);
     auto mix = [&](int m, cx<T> z, cx<T> zp) -> cx<T> {
         const T al = ab[3 * m];
         const cx<T> be{ab[3 * m + 1], ab[3 * m + 2]};
@@ -438,7 +451,10 @@ __device__ __forceinline__ void pair_diffuse(cx<T> (&a)[N1], int t, cx<T>* __res
         cx<T> b[N1];
         sfor<0, N1>([&](auto K) {
             constexpr int m = decltype(K)::value;
-            b[m] = mix(m, a[m], a[(N - m) % N]);
+            if constexpr (kMean && m == 0)
+                b[0] = mean_over_n<N>(a[0]);
+            else
+                b[m] = mix(m, a[m], a[(N - m) % N]);
         });
         sfor<0, N1>([&](auto K) { a[decltype(K)::value] = b[decltype(K)::value]; });
         dft<N1, true>(a);
@@ -469,6 +485,8 @@ __device__ __forceinline__ void pair_diffuse(cx<T> (&a)[N1], int t, cx<T>* __res
                 constexpr int k2 = decltype(K2)::value;
                 const int k2p = (k1 == 0) ? (N2 - k2) % N2 : N2 - 1 - k2;
                 z[i][k2] = mix(k1 + N1 * k2, sh[lay(k1, k2)], sh[lay(k1p, k2p)]);
+                if constexpr (kMean && i == 0 && k2 == 0)
+                    if (t == 0) z[0][0] = mean_over_n<N>(sh[lay(0, 0)]);
             });
         });
         __syncthreads();

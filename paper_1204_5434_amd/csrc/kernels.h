@@ -109,7 +109,7 @@ __device__ __forceinline__ void line_diffuse(cx<T> (&a)[N1], int t, cx<T>* __res
     if constexpr (EXT == 0)
         diffuse<N1, N2, MEAN>(a, t, sh, lay, g);
     else
-        pair_diffuse<N1, N2>(a, t, sh, lay, g);
+        pair_diffuse<N1, N2, MEAN && EXT == 1>(a, t, sh, lay, g);
 }
 
 // The Richardson combination (4 u - v) / 3 of Eq. (12).  In complex float it
