@@ -419,7 +419,8 @@ pft_status pft_batch_sync(pft_batch* batch);
  * Errors: PFT_E_INVALID, PFT_E_UNSUPPORTED, PFT_E_NOMEM, PFT_E_DEVICE. */
 pft_status pft_autotune(int32_t precision, const int32_t* sizes, int32_t nsizes, void* hip_stream,
                         int32_t* choices, double* timings);
-/* Save / load the table (text: "arch precision N kind variant" per line;
+/* Save / load the table (text: "arch precision N kind variant" per line, variant
+ * -1 for what was neither tuned nor loaded and so keeps the library's own choice;
  * entries for another GPU architecture are ignored).  pft_create also loads
  * the file named by $PFT_TUNE_CACHE once per process.  Errors: PFT_E_INVALID
  * (NULL path or file not writable / readable). */

@@ -207,7 +207,7 @@ pft_status pft_tune_save(const char* path)
         for (int n = 0; n <= 256; ++n)
             for (int kind = 0; kind < 3; ++kind)
                 if (pft::axis_supported(n))
-                    std::fprintf(f, "%s %d %d %d %d\n", arch.c_str(), prec, n, kind, tuned_variant(prec, n, kind));
+                    std::fprintf(f, "%s %d %d %d %d\n", arch.c_str(), prec, n, kind, g_tune[prec][n][kind]);
     std::fclose(f);
     return PFT_OK;
 }
@@ -223,7 +223,7 @@ pft_status pft_tune_load(const char* path)
     while (std::fscanf(f, "%63s %d %d %d %d", a, &prec, &n, &kind, &v) == 5) {
         int n1, n2, w;
         if (arch == a && (prec == 0 || prec == 1) && kind >= 0 && kind <= 2 && n >= 0 && n <= 256 &&
-            pft::axis_variant(n, v, &n1, &n2, &w))
+            (v == -1 ? pft::axis_supported(n) : pft::axis_variant(n, v, &n1, &n2, &w)))
             g_tune[prec][n][kind] = v;
     }
     std::fclose(f);

@@ -73,3 +73,34 @@ def test_null_context_and_plan_errors(pft):
     assert lib.pft_contour_plan(1, 0.5, h.ctypes.data, b.ctypes.data, J.ctypes.data) == -1
     assert lib.pft_contour_plan(3, 1.5, h.ctypes.data, b.ctypes.data, J.ctypes.data) == -1
     assert lib.pft_noise_words(0, 0, 0, 0, 0, None, None) == pft.PFT_E_INVALID
+
+
+def test_tuning_file_leaves_untuned_lengths_untuned(pft, tmp_path):
+    """A saved table says what was tuned and what was not, so that a process that
+    loads it chooses the same kernels as the one that saved it."""
+    def saved(name):
+        pft.pft_tune_save(str(tmp_path / name))
+        lines = [l.split() for l in open(tmp_path / name)]
+        return lines[0][0], {tuple(map(int, l[1:4])): int(l[4]) for l in lines}
+
+    def load(entries):
+        path = tmp_path / "entries"
+        path.write_text("".join(f"{arch} {p} {n} {k} {v}\n" for (p, n, k), v in entries.items()))
+        pft.pft_tune_load(str(path))
+
+    arch, before = saved("before")
+    every = {(p, n, k) for p in (0, 1) for n in pft.SUPPORTED_AXES for k in range(3)}
+    assert set(before) == every
+    load(dict.fromkeys(every, -1))
+    assert set(saved("none")[1].values()) == {-1}
+    tuned = {(0, 24, 0): 1, (1, 128, 2): 0}
+    load(tuned)
+    _, table = saved("some")
+    assert {k: v for k, v in table.items() if v != -1} == tuned
+    load({(0, 24, 0): 3, (1, 100, 0): -1, (0, 32, 0): -2})  # no such variant, length or variant
+    assert saved("same")[1] == table
+    load(dict.fromkeys(every, -1))
+    pft.pft_tune_load(str(tmp_path / "some"))
+    assert saved("again")[1] == table
+    pft.pft_tune_load(str(tmp_path / "before"))
+    assert saved("end")[1] == before
