@@ -222,7 +222,8 @@ pft_status pft_propagate(pft_ctx* ctx, const double* w_plus, const double* w_min
 pft_status pft_densities(pft_ctx* ctx, double* phi_a, double* phi_b, double* Q);
 
 /* pft_propagate followed by pft_densities on these buffers, replayed from a
- * HIP graph: the first call (and any call with other buffers) captures one
+ * HIP graph: the first call (and any call with other buffers, or after
+ * pft_set_variant, pft_set_fused_planes or pft_set_concurrent_sweeps) captures one
  * evaluation, both sweeps' streams included, into a graph the context owns;
  * every call then enqueues nreps replays (0: capture only) after the work
  * already on the context stream, and later work on that stream waits for them.

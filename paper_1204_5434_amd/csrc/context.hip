@@ -1007,6 +1007,7 @@ pft_status pft_set_concurrent_sweeps(pft_ctx* c, int32_t on)
         if (!c->s2) return c->fail(PFT_E_UNSUPPORTED, "this context was created without a second stream");
         c->dual_off = false;
     }
+    ++c->sched;
     return PFT_OK;
 }
 
@@ -1018,6 +1019,7 @@ pft_status pft_set_fused_planes(pft_ctx* c, int32_t on)
         return c->fail(PFT_E_UNSUPPORTED, "no fused yz-plane pass for a %d x %d plane in this precision", c->p.ny, c->p.nz);
     c->fused = on != 0;
     c->fused_conj_only = on == 2;
+    ++c->sched;
     return PFT_OK;
 }
 
@@ -1067,7 +1069,8 @@ pft_status pft_evaluate_graph(pft_ctx* c, const double* wp, const double* wm, do
     if (!aligned16(wp) || (need_wm && !aligned16(wm)) || !aligned16(phi_a) || !aligned16(phi_b) || (Q && !aligned16(Q)))
         return c->fail(PFT_E_INVALID, "w_plus/w_minus/phi_a/phi_b must be non-null and 16-byte aligned (Q aligned if given)");
     const void* key[5] = {wp, need_wm ? wm : nullptr, phi_a, phi_b, Q};
-    if (!c->gexec || std::memcmp(key, c->gkey, sizeof key) != 0) {
+    if (!c->gexec || c->gsched != c->sched || std::memcmp(key, c->gkey, sizeof key) != 0) {
+        if (c->gs) PFT_HIP(c, hipStreamSynchronize(c->gs));  // an earlier replay may still run
         if (c->gexec) (void)hipGraphExecDestroy(c->gexec);
         if (c->graph) (void)hipGraphDestroy(c->graph);
         c->gexec = nullptr;
@@ -1104,6 +1107,7 @@ pft_status pft_evaluate_graph(pft_ctx* c, const double* wp, const double* wm, do
         }
         c->graph = g;
         std::memcpy(c->gkey, key, sizeof key);
+        c->gsched = c->sched;
     }
     if (nreps == 0) return PFT_OK;
     PFT_HIP(c, hipEventRecord(c->ev_g0, c->stream));

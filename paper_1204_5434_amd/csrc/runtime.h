@@ -100,12 +100,14 @@ struct pft_ctx {
     double2* adjG = nullptr;    // [A sum][A comp][B sum][B comp], M each
     double2* adjAcc = nullptr;  // [3][nparts] box-derivative partials
     // graph replay of one evaluation (pft_evaluate_graph): captured on gs for
-    // the buffers in gkey, replayed there between two events
+    // the buffers in gkey and the schedule of then (gsched), replayed there
+    // between two events
     hipStream_t gs = nullptr;
     hipGraph_t graph = nullptr;
     hipGraphExec_t gexec = nullptr;
     hipEvent_t ev_g0 = nullptr, ev_g1 = nullptr;
     const void* gkey[5] = {};
+    uint64_t sched = 0, gsched = 0;  // sched counts the changes of schedule or variant
     // profiling: event pairs recorded around each launch while prof is set
     bool prof = false;
     std::vector<hipEvent_t> ev;

@@ -238,6 +238,7 @@ pft_status pft_set_variant(pft_ctx* c, int32_t axis, int32_t variant)
     if (!pft::axis_variant(n, variant, &n1, &n2, &w)) return c->fail(PFT_E_UNSUPPORTED, "no variant %d for %d", variant, n);
     c->var[axis] = variant;
     c->m[axis] = false;  // that axis's pass now runs the variant
+    ++c->sched;
     return PFT_OK;
 }
 

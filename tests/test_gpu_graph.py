@@ -122,3 +122,34 @@ def test_graph_replay_rejections():
     assert e.value.status == B.PFT_E_STATE
     ctx.pft_profile_end()
     ctx.close()
+
+
+@pytest.mark.parametrize("prec", [B.PFT_C128, B.PFT_C64], ids=["c128", "c64"])
+def test_graph_follows_schedule_and_variants(prec):
+    """A replay after a change of schedule or variant is that of an evaluation
+    with it, not of the graph captured before.  An axis on the matrix cores differs
+    in rounding from the line transforms, and the fused pass of such a plane from
+    its axis passes once y runs by them."""
+    n = (32, 24, 24)
+    say("graph after settings", n, prec)
+    a, b = fields(n, 8)
+    ctx = B.Context(B.Params(*n, 4.0, 3.0, 3.0, 10, 0.37, 14.0, 2.0, prec))
+    out, ref = ([torch.empty(n, dtype=torch.complex128, device=DEV) for _ in range(2)] for _ in range(2))
+    ctx.pft_evaluate_graph(a, b, *out)
+    seen = []
+    for setting in (lambda: None, lambda: ctx.pft_set_variant(0, 1), lambda: ctx.pft_set_variant(1, 1),
+                    lambda: ctx.pft_set_fused_planes(0), lambda: ctx.pft_set_fused_planes(1),
+                    lambda: ctx.pft_set_concurrent_sweeps(False), lambda: ctx.pft_set_concurrent_sweeps(True)):
+        setting()
+        for _ in range(3):
+            for t in out:
+                t.zero_()
+            ctx.pft_evaluate_graph(a, b, *out, nreps=2)
+            torch.cuda.synchronize()
+            ctx.pft_propagate(a, b)
+            ctx.pft_densities(*ref)
+            torch.cuda.synchronize()
+            assert torch.equal(out[0], ref[0]) and torch.equal(out[1], ref[1]), len(seen)
+        seen.append(ref[0].clone())
+    assert not torch.equal(seen[0], seen[1]) and not torch.equal(seen[2], seen[3])
+    ctx.close()
