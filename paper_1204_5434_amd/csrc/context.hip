@@ -541,12 +541,23 @@ static bool fused_default(const pft_params& p)
 // sweeps 32 planes 48.5 / 46.5, 64 planes 51.0 / 57.6, one 42.3 / 38.9 and 48.8 /
 // 49.8, 80 x 80 alike; complex double 80 x 80, two sweeps 32 planes 56.6 / 51.6, 64
 // planes 64.0 / 61.6, 96 planes 81.3 / 87.2, one 52.6 / 40.2, 58.4 / 52.2, 67.2 / 64.4
-// and with 128 planes 66.5 / 68.5.  A sweep that waits for its copies to the host
+// and with 128 planes 66.5 / 68.5.  The plain split step, whose fused pass makes up
+// less of a step: complex float 128 x 128, two sweeps 40 planes 30.7 / 30.4, 48 planes
+// 30.3 / 31.4, 64 planes 34.0 / 37.0, one 128 planes 33.6 / 32.5, 192 planes 39.5 / 41.5;
+// 96 x 96, two sweeps 24 planes 23.3 / 22.2, 32 planes 24.1 / 24.5, one 20.4 / 20.4 and
+// 21.2 / 21.3; 80 x 80, two sweeps 16 planes 17.9 / 18.5, one 15.6 / 16.8; complex
+// double 80 x 80, two sweeps 48 planes 30.8 / 28.7, 64 planes 31.6 / 32.1, one 96 planes
+// 33.8 / 33.2, 128 planes 33.8 / 35.9.
+// A sweep that waits for its copies to the host
 // (storage in host memory) keeps the fused pass: 128^3 complex float, 148 / 157 ms
 // per evaluation.
 static bool few_planes(const pft_params& p, int sweeps)
 {
     if (p.bc[1] || p.bc[2]) return false;
+    if (p.scheme == PFT_SPLIT2) {
+        if (p.precision == PFT_C128) return p.nx <= (sweeps == 2 ? 48 : 96);
+        return p.ny >= 128 ? p.nx <= (sweeps == 2 ? 40 : 128) : p.ny == 96 && p.nx <= 24;
+    }
     if (p.precision == PFT_C128) return p.nx * sweeps <= (sweeps == 2 ? 128 : 96);
     return p.ny >= 128 ? p.nx * sweeps <= 128 : p.nx <= 32;
 }
