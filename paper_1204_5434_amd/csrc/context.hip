@@ -562,6 +562,36 @@ static bool few_planes(const pft_params& p, int sweeps)
     return p.ny >= 128 ? p.nx * sweeps <= 128 : p.nx <= 32;
 }
 
+// Whether an axis pass by line transforms is faster than on the matrix cores, on
+// grids that don't share their launches (us per contour step, both sweeps, matrix
+// cores / line transforms; the columns are those of the other two axes).
+// Complex float, x and y: from 16384 columns on a sweep's workgroups of 64 fill the
+// device, and what counts is no longer the latency of one but the arithmetic, which
+// from 48 points on is more than the line transforms'.  y, 48 points: 96 x 128 columns
+// 56.3 / 57.8, 128 x 128 57.0 / 53.8, 192 x 128 74.3 / 73.7; 64 points 63.0 / 63.0, 68.5 /
+// 64.6, 87.8 / 87.9; 80 points 72.3 / 72.1, 78.5 / 77.1, 111.6 / 107.2; 96 points 78.6 / 79.8,
+// 89.1 / 88.8, 123.5 / 123.1.  x, 48 points 55.7 / 57.1, 57.3 / 52.8, 75.8 / 73.1; 64
+// points alike, 80 points 75.2 / 75.3, 96 points 80.7 / 81.9; the plain split step alike.
+// At 40 points 52.9 / 57.5 and 69.5 / 72.6.  Between walls alike at 48 and 64 points, at
+// 80 points x 77.3 / 79.7, y 82.1 / 83.3.
+// Complex float, z between walls: 80 points 77.6 / 76.4 at 96 x 128 columns, 118.7 / 114.7 at
+// 192 x 128; 64 points 72.0 / 74.4 and 104.7 / 101.9, in the plain split step 39.7 / 38.4 and
+// 52.3 / 47.9.
+// Complex double, periodic z: 48 points 88.0 / 87.5 at 128 x 128 columns, 130.2 / 125.1 at
+// 192 x 128, in the plain split step 45.5 / 43.0 and 60.9 / 60.4; 64 points 90.0 / 92.2 at
+// 128 x 96, 107.8 / 107.7 at 128 x 128, 170.3 / 155.3 at 192 x 128, in the plain split step
+// 43.4 / 39.3 at 96 x 96 and 81.2 / 75.9.
+static bool lines_faster(const pft_params& p, int ax)
+{
+    const int n[3] = {p.nx, p.ny, p.nz};
+    const int64_t cols = (int64_t)p.nx * p.ny * p.nz / n[ax];
+    const bool wall = p.bc[ax] != 0, split2 = p.scheme == PFT_SPLIT2;
+    if (p.precision == PFT_C128)
+        return ax == 2 && !wall && (n[2] == 48 || (n[2] == 64 && (split2 || cols > 16384)));
+    if (ax == 2) return wall && (n[2] == 80 || (n[2] == 64 && split2));
+    return cols >= 16384 && n[ax] >= 48 && n[ax] <= (ax == 1 && !wall ? 96 : 64);
+}
+
 pft_status create_ctx(const pft_params* params, void* hip_stream, bool dual, pft_ctx** out)
 {
     if (!out) return PFT_E_INVALID;
@@ -619,6 +649,9 @@ pft_status create_ctx(const pft_params* params, void* hip_stream, bool dual, pft
     // between walls the axis passes on the matrix cores beat the line transforms' fused pass
     c->fused = c->mplane || (!((p.bc[1] || p.bc[2]) && c->m[1] && c->m[2]) &&
                              !((alone || dual) && few_planes(p, alone ? 1 : 2)) && fused_default(p));
+    if (!c->together) {
+        for (int ax = 0; ax < 3; ++ax) c->m[ax] = c->m[ax] && !lines_faster(p, ax);
+    }
     c->stream = static_cast<hipStream_t>(hip_stream);
     // table slot length: n factors per periodic axis, 3n per walled axis
     c->maxN = std::max((p.bc[0] ? 3 : 1) * p.nx, std::max((p.bc[1] ? 3 : 1) * p.ny, (p.bc[2] ? 3 : 1) * p.nz));

@@ -122,3 +122,31 @@ def test_constant_and_nonfinite_fields(prec):
         assert c2.pft_status_flags() & 1
         c2.close()
     ctx.close()
+
+
+# which passes of large grids run by line transforms, on both sides of each line:
+# (grid, walls, precision, scheme, axis, by lines)
+LINES = [((128, 48, 128), (0, 0, 0), 1, 0, 1, True), ((96, 48, 128), (0, 0, 0), 1, 0, 1, False),
+         ((128, 40, 128), (0, 0, 0), 1, 0, 1, False), ((128, 96, 128), (0, 0, 0), 1, 1, 1, True),
+         ((64, 128, 128), (0, 0, 0), 1, 0, 0, True), ((80, 192, 128), (0, 0, 0), 1, 0, 0, False),
+         ((128, 64, 128), (0, 2, 0), 1, 0, 1, True), ((128, 80, 128), (0, 1, 0), 1, 0, 1, False),
+         ((96, 96, 80), (0, 0, 1), 1, 0, 2, True), ((96, 96, 64), (0, 0, 2), 1, 0, 2, False), ((96, 96, 64), (0, 0, 2), 1, 1, 2, True),
+         ((96, 96, 48), (0, 0, 0), 0, 0, 2, True), ((24, 20, 48), (0, 0, 0), 0, 0, 2, False), ((96, 96, 40), (0, 0, 0), 0, 0, 2, False),
+         ((128, 128, 64), (0, 0, 0), 0, 0, 2, False), ((192, 96, 64), (0, 0, 0), 0, 0, 2, True), ((96, 80, 64), (0, 0, 0), 0, 1, 2, True)]
+
+
+@pytest.mark.parametrize("n,bc,prec,scheme,axis,lines", LINES)
+def test_passes_of_large_grids(n, bc, prec, scheme, axis, lines):
+    """The pass an axis runs by default equals the line transforms' bit for bit
+    where it is one, and otherwise agrees with it to rounding."""
+    print("passes of large grids", n, bc, prec, scheme, axis, flush=True)
+    g = torch.Generator(device=DEV).manual_seed(n[axis])
+    w = [0.2 * torch.randn(n, dtype=torch.complex128, device=DEV, generator=g) for _ in range(2)]
+    ctx = B.Context(B.Params(*n, *[0.1 * a for a in n], 3, 0.5, 14.0, 1.0, prec, scheme, B.PFT_DIBLOCK, 0.0, 0, bc))
+    assert ctx.pft_fused_planes() == 0
+    got = ctx.evaluate(*w)["phiA"]
+    ctx.pft_set_variant(axis, 0)
+    ref = ctx.evaluate(*w)["phiA"]
+    ctx.close()
+    assert torch.equal(got, ref) == lines
+    assert (got - ref).abs().max() <= (1e-12 if prec == B.PFT_C128 else 2e-5) * ref.abs().max()
