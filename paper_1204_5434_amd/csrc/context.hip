@@ -548,9 +548,8 @@ static bool fused_default(const pft_params& p)
 // 21.2 / 21.3; 80 x 80, two sweeps 16 planes 17.9 / 18.5, one 15.6 / 16.8; complex
 // double 80 x 80, two sweeps 48 planes 30.8 / 28.7, 64 planes 31.6 / 32.1, one 96 planes
 // 33.8 / 33.2, 128 planes 33.8 / 35.9.
-// A sweep that waits for its copies to the host
-// (storage in host memory) keeps the fused pass: 128^3 complex float, 148 / 157 ms
-// per evaluation.
+// A sweep that waits for its copies to the host (storage in host memory) keeps the
+// fused pass: 128^3 complex float, 148 / 157 ms per evaluation.
 static bool few_planes(const pft_params& p, int sweeps)
 {
     if (p.bc[1] || p.bc[2]) return false;
@@ -560,6 +559,27 @@ static bool few_planes(const pft_params& p, int sweeps)
     }
     if (p.precision == PFT_C128) return p.nx * sweeps <= (sweeps == 2 ? 128 : 96);
     return p.ny >= 128 ? p.nx * sweeps <= 128 : p.nx <= 32;
+}
+
+// Variant of an x pass by line transforms that was not tuned (us per contour step,
+// both sweeps, variant 0 / this one).
+// Complex double, 128 points, two waves per SIMD: 128^3 191.6 / 185.9, 128 x 40 x 40
+// 37.9 / 36.5, 128 x 96 x 192 235.9 / 228.5, 128 x 80 x 96 115.3 / 115.7, 128 x 64 x 48
+// 57.0 / 57.4; beside walled z lines 195.0 / 197.7.  Complex float beside the fused
+// plane pass: 128^3 89.0 / 88.7.
+// Complex double, 256 points, the wide tile, where the arrays exceed the Infinity
+// Cache: 256^3 1834.6 / 1806.9, 256 x 128 x 256 915.4 / 902.5; 256 x 128 x 128 448.7 /
+// 453.3, 256 x 80 x 96 216.1 / 220.7.
+// The same variants of y and z passes, and of complex float on the axis schedule,
+// stay within 1% at 128 points; at 256 z within 1%, y 1810.0 / 1814.9, x in complex
+// float 924.0 / 970.0.  Wide tiles of other lengths lose 0 to 10%; 64 points split
+// 8 x 8 gain 2 to 10% (z, 128 x 128 lines: 108.6 / 103.7, complex float 70.1 / 62.8),
+// which is left to the tuner.
+static int untuned_x_variant(const pft_params& p, bool fused)
+{
+    if (p.precision != PFT_C128) return fused && p.nx == 128 && !p.bc[1] && !p.bc[2] ? 2 : 0;
+    const double bytes = 16.0 * p.nx * p.ny * p.nz;
+    return p.nx == 128 && !p.bc[2] ? 2 : p.nx == 256 && bytes >= 128.0 * (1 << 20) ? 1 : 0;
 }
 
 // Whether an axis pass by line transforms is faster than on the matrix cores, on
@@ -624,10 +644,8 @@ pft_status create_ctx(const pft_params* params, void* hip_stream, bool dual, pft
         delete c;
         return PFT_E_DEVICE;
     }
-    const bool walls = p.bc[2] || (p.precision == PFT_C64 && p.bc[1]);
-    c->var[0] = tuned_variant(p.precision, p.nx, 1, walls);
-    c->var[1] = tuned_variant(p.precision, p.ny, 2, walls);
-    c->var[2] = tuned_variant(p.precision, p.nz, 0, walls);
+    c->var[1] = tuned_variant(p.precision, p.ny, 2);
+    c->var[2] = tuned_variant(p.precision, p.nz, 0);
     const bool dbl = p.precision == PFT_C128;
     c->mplane = p.ny == p.nz && !p.bc[1] && !p.bc[2] &&
                 (dbl ? pft::mplane_supported<double>(p.ny) : pft::mplane_supported<float>(p.ny));
@@ -649,6 +667,7 @@ pft_status create_ctx(const pft_params* params, void* hip_stream, bool dual, pft
     // between walls the axis passes on the matrix cores beat the line transforms' fused pass
     c->fused = c->mplane || (!((p.bc[1] || p.bc[2]) && c->m[1] && c->m[2]) &&
                              !((alone || dual) && few_planes(p, alone ? 1 : 2)) && fused_default(p));
+    c->var[0] = tuned_variant(p.precision, p.nx, 1, untuned_x_variant(p, c->fused));
     if (!c->together) {
         for (int ax = 0; ax < 3; ++ax) c->m[ax] = c->m[ax] && !lines_faster(p, ax);
     }

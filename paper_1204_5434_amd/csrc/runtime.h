@@ -739,9 +739,9 @@ namespace pft::rt {
 // Contour plan (see pft_contour_plan): step lengths, blocks and the junction node.
 int contour_plan(int ns, double f, double* h, int* blk, int* junction);
 // Kernel variant of an axis pass per (precision, axis length, kind: 0 = z
-// pass, 1 = x pass, 2 = y pass) for contexts created from now on (autotuner).
-// walls: the grid has some that the untuned choice was not made for
-int tuned_variant(int prec, int n, int kind, bool walls = false);
+// pass, 1 = x pass, 2 = y pass) for contexts created from now on (autotuner);
+// `untuned` where it was neither tuned nor loaded.
+int tuned_variant(int prec, int n, int kind, int untuned = 0);
 void tune_env_once();
 pft_status create_ctx(const pft_params* params, void* hip_stream, bool dual, pft_ctx** out);
 void free_all(pft_ctx* c);

@@ -19,26 +19,13 @@ struct Tune {
 } g_tuned;
 auto& g_tune = g_tuned.v;
 std::once_flag g_tune_env;
-
-// Without either: lines of 128 points on kernels bounded to two waves per SIMD
-// (cube, both sweeps on two streams: complex double 200.8 -> 190.5 us per contour
-// step, complex float 111.3 -> 107.9), and the x and y passes of 256 points in
-// complex double on the wide tile (1888 -> 1841 us).  Beside walled z lines they
-// gain nothing (128^3 complex double 195.0 / 197.7 us, beside walled y lines 187.7 /
-// 183.2; complex float 94.3 / 94.9).
-int default_variant(int prec, int n, int kind)
-{
-    if (n == 128) return 2;
-    if (n == 256 && prec == PFT_C128 && kind > 0) return 1;
-    return 0;
-}
 }  // namespace
 
-int tuned_variant(int prec, int n, int kind, bool walls)
+int tuned_variant(int prec, int n, int kind, int untuned)
 {
     int n1, n2, w;
     int v = (n >= 0 && n <= 256) ? g_tune[prec & 1][n][kind] : 0;
-    if (v < 0) v = walls ? 0 : default_variant(prec & 1, n, kind);
+    if (v < 0) v = untuned;
     return pft::axis_variant(n, v, &n1, &n2, &w) ? v : 0;
 }
 
