@@ -352,27 +352,44 @@ __device__ __forceinline__ void dft(cx<T>* v)
 // error that grows linearly with the number of steps in Q (complex double, a film
 // of 80 x 96 x 40 points whose y axis alone runs here, 76 steps, against 80-bit
 // arithmetic: Q off by 1.4e-14 with the rounded 1/96, 4e-15 without it).
-// Complex float divides in double; complex double adds what 1/N lost to rounding.
+// Periodic lines of complex float divide in double; the others add what 1/N lost
+// to rounding (mean_rest times the mode, without a branch: with one the compiler kept
+// fewer factors in flight, and a 96-point y pass in complex double lost 3%).
 constexpr bool power_of_two(int n) { return (n & (n - 1)) == 0; }
 template <int N, typename T>
 __device__ __forceinline__ cx<T> mean_over_n(cx<T> x)
 {
     constexpr double inv = 1.0 / N;
+    return {T(double(x.re) * inv), T(double(x.im) * inv)};
+}
+template <int N, typename T>
+constexpr T mean_rest()
+{
+    constexpr double inv = 1.0 / N;
     if constexpr (std::is_same<T, float>::value) {
-        return {T(double(x.re) * inv), T(double(x.im) * inv)};
+        return T(inv - double(T(inv)));
     } else {
-        // 1/N - inv, from products that are exact: N times each half of inv's digits
+        // from products that are exact: N times each half of inv's digits
         constexpr double up = inv * 134217729.0, head = up - (up - inv), tail = inv - head;
-        constexpr double rest = ((1.0 - N * head) - N * tail) / N;
-        return {__builtin_fma(x.re, inv, x.re * rest), __builtin_fma(x.im, inv, x.im * rest)};
+        return ((1.0 - N * head) - N * tail) / N;
     }
+}
+
+// (g + rest) x + y with one rounding of the sum: g x rounded by itself would round
+// the rest away again.
+template <typename T>
+__device__ __forceinline__ cx<T> times_sum(T g, T rest, cx<T> x, cx<T> y = cx<T>{T(0), T(0)})
+{
+    return {fma(g, x.re, fma(rest, x.re, y.re)), fma(g, x.im, fma(rest, x.im, y.im))};
 }
 
 template <int N1, int N2, bool MEAN = false, typename T, class Lay, class G>
 __device__ __forceinline__ void diffuse(cx<T> (&a)[N1], int t, cx<T>* __restrict__ sh, const Lay& lay, const G& g)
 {
     constexpr int N = N1 * N2;
-    constexpr bool kMean = MEAN && (std::is_same<T, float>::value || !power_of_two(N));
+    constexpr bool kMean = MEAN && std::is_same<T, float>::value;
+    constexpr bool kRest = MEAN && !kMean && !power_of_two(N);
+    const T rest = kRest && t == 0 ? mean_rest<N, T>() : T(0);
     if constexpr (N2 == 1) {
         dft<N1, false>(a);
         sfor<0, N1>([&](auto K) {
@@ -381,7 +398,10 @@ __device__ __forceinline__ void diffuse(cx<T> (&a)[N1], int t, cx<T>* __restrict
                 a[0] = mean_over_n<N>(a[0]);
             } else {
                 const T gk = g[k];
-                a[k] = gk * a[k];
+                if constexpr (kRest && k == 0)
+                    a[0] = times_sum(gk, rest, a[0]);
+                else
+                    a[k] = gk * a[k];
             }
         });
         dft<N1, true>(a);
@@ -406,6 +426,8 @@ __device__ __forceinline__ void diffuse(cx<T> (&a)[N1], int t, cx<T>* __restrict
                 const T gk = g[k1 + N1 * k2];
                 if constexpr (kMean && i == 0 && k2 == 0)
                     b[0] = (t == 0) ? mean_over_n<N>(b[0]) : gk * b[0];  // k1 = t: lane 0 holds k = 0
+                else if constexpr (kRest && i == 0 && k2 == 0)
+                    b[0] = times_sum(gk, rest, b[0]);
                 else
                     b[k2] = gk * b[k2];
             });
@@ -440,21 +462,28 @@ __device__ __forceinline__ void pair_diffuse(cx<T> (&a)[N1], int t, cx<T>* __res
                                              const T* __restrict__ ab)
 {
     constexpr int N = N1 * N2;
-    constexpr bool kMean = MEAN && !power_of_two(N);
+    constexpr bool kRest = MEAN && !power_of_two(N);
+    const T rest = kRest && t == 0 ? mean_rest<N, T>() : T(0);
     auto mix = [&](int m, cx<T> z, cx<T> zp) -> cx<T> {
         const T al = ab[3 * m];
         const cx<T> be{ab[3 * m + 1], ab[3 * m + 2]};
         return al * z + be * zp;
+    };
+    // the lane's first frequency, m = 0 where rest is not 0
+    auto mix0 = [&](int m, cx<T> z, cx<T> zp) -> cx<T> {
+        if constexpr (kRest) {
+            const cx<T> be{ab[3 * m + 1], ab[3 * m + 2]};
+            return times_sum(ab[3 * m], rest, z, be * zp);
+        } else {
+            return mix(m, z, zp);
+        }
     };
     if constexpr (N2 == 1) {
         dft<N1, false>(a);
         cx<T> b[N1];
         sfor<0, N1>([&](auto K) {
             constexpr int m = decltype(K)::value;
-            if constexpr (kMean && m == 0)
-                b[0] = mean_over_n<N>(a[0]);
-            else
-                b[m] = mix(m, a[m], a[(N - m) % N]);
+            b[m] = m == 0 ? mix0(0, a[0], a[0]) : mix(m, a[m], a[(N - m) % N]);
         });
         sfor<0, N1>([&](auto K) { a[decltype(K)::value] = b[decltype(K)::value]; });
         dft<N1, true>(a);
@@ -484,9 +513,10 @@ __device__ __forceinline__ void pair_diffuse(cx<T> (&a)[N1], int t, cx<T>* __res
             sfor<0, N2>([&](auto K2) {
                 constexpr int k2 = decltype(K2)::value;
                 const int k2p = (k1 == 0) ? (N2 - k2) % N2 : N2 - 1 - k2;
-                z[i][k2] = mix(k1 + N1 * k2, sh[lay(k1, k2)], sh[lay(k1p, k2p)]);
-                if constexpr (kMean && i == 0 && k2 == 0)
-                    if (t == 0) z[0][0] = mean_over_n<N>(sh[lay(0, 0)]);
+                if constexpr (i == 0 && k2 == 0)
+                    z[0][0] = mix0(k1, sh[lay(k1, 0)], sh[lay(k1p, k2p)]);
+                else
+                    z[i][k2] = mix(k1 + N1 * k2, sh[lay(k1, k2)], sh[lay(k1p, k2p)]);
             });
         });
         __syncthreads();
