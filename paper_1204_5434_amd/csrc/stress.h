@@ -15,13 +15,16 @@
 // and reduced once at the end.
 //
 // Each capture of a tile of lines is a workgroup of its own, for the number of
-// wavefronts in flight.  The three of a tile share E4 and lambda: they are
-// numbered so that they follow each other on one XCD (workgroups go round the
-// XCDs in order) and find those in its L2 (96^3 complex double, a strided pass
-// beside the recomputation's: 28.7 us with all workgroups of a capture in a row,
-// 27.1 us so).  What bounds it is the chain of loads, transform and loads; E4 and
-// lambda requested before the transform cost more registers than they hide
-// (gradient 40.2 -> 40.8 ms), and so did the accumulation of dH/dw as a fourth
+// wavefronts in flight.  The three of a tile share E4 and lambda.  On large grids
+// they are numbered so that they follow each other on one XCD (workgroups go round
+// the XCDs in order) and find those in its L2; from the Infinity Cache, which holds
+// the arrays of smaller ones, they are as quick, and there the workgroups of a
+// capture are in a row.  Reverse mode with the box stress, ms, in a row / so: complex
+// double 128^3 13.85 / 13.35, 256 x 64 x 64 7.72 / 7.52, 96^3 between walls 8.27 / 8.17,
+// 64^3 2.75 / 2.77, 32 x 128 x 128 4.59 / 4.64; complex float 128^3 7.68 / 7.60, 96^3 5.54 /
+// 5.56, 80 x 96 x 40 3.59 / 3.64.  What bounds it is the chain of loads, transform and
+// loads; E4 and lambda requested before the transform cost more registers than they
+// hide (gradient 40.2 -> 40.8 ms), and so did the accumulation of dH/dw as a fourth
 // workgroup of the z pass (46.7 ms).
 // Along a walled axis (EXT = 1 reflecting, 2 absorbing) the modes are
 // k = pi m / L_a, which scale with 1/L_a as well, so the same sum holds with
@@ -55,15 +58,20 @@ struct StressPass {
     double2* part;      // one slot per workgroup, accumulated
 };
 
-// Tile and row of this workgroup: the rows of a tile are kXcds apart.
+// Tile and row of this workgroup: NEAR, the rows of a tile are kXcds apart, else
+// blockIdx.y.
 constexpr int kXcds = 8;
+constexpr int64_t kNearBytes = 12 << 20;  // arrays of at least this size are NEAR
+template <bool NEAR>
 struct StressTile {
-    int tile, row;
+    int tile = (int)blockIdx.x, row = (int)blockIdx.y;
     __device__ __forceinline__ explicit StressTile(int rows)
     {
-        const int group = (int)blockIdx.x / kXcds;
-        row = group % rows;
-        tile = group / rows * kXcds + (int)blockIdx.x % kXcds;
+        if constexpr (NEAR) {
+            const int group = tile / kXcds;
+            row = group % rows;
+            tile = group / rows * kXcds + tile % kXcds;
+        }
     }
 };
 
@@ -120,7 +128,7 @@ __device__ __forceinline__ double2 stress_partner(const StressPass<T>& A, int i,
 }
 
 // Lines along z (contiguous), laid out as in the z pass.
-template <typename T, int N1, int N2, int EXT>
+template <typename T, int N1, int N2, int EXT, bool NEAR>
 __global__ __launch_bounds__((ZShape<N1, N2, 1>::kThreads)) void k_stress_z(StressPass<T> A)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -129,8 +137,8 @@ __global__ __launch_bounds__((ZShape<N1, N2, 1>::kThreads)) void k_stress_z(Stre
     constexpr int N = N1 * N2;
     constexpr int LPW = ZShape<N1, N2, 1>::kLines;
     const int t = threadIdx.x % N2, l = threadIdx.x / N2;
-    const StressTile b(A.rows);
-    if (b.tile >= A.ntile) return;
+    const StressTile<NEAR> b(A.rows);
+    if (NEAR && b.tile >= A.ntile) return;
     const int64_t line = (int64_t)b.tile * LPW + l;
     const bool act = line < A.nlines;
     auto pos = [&](int r) { return line * N + ext_index<EXT, N>(r * N2 + t); };
@@ -160,7 +168,7 @@ __global__ __launch_bounds__((ZShape<N1, N2, 1>::kThreads)) void k_stress_z(Stre
 }
 
 // Strided lines along x or y, laid out as in the strided passes.
-template <typename T, int N1, int N2, int EXT>
+template <typename T, int N1, int N2, int EXT, bool NEAR>
 __global__ __launch_bounds__((SShape<T, N2, 1>::kThreads)) void k_stress_s(StressPass<T> A)
 {
     constexpr int N = N1 * N2;
@@ -170,8 +178,8 @@ __global__ __launch_bounds__((SShape<T, N2, 1>::kThreads)) void k_stress_s(Stres
     __shared__ double2 red[NT];
     cx<T>* sh = reinterpret_cast<cx<T>*>(smem_raw);
     const int c = threadIdx.x % TC, t = threadIdx.x / TC;
-    const StressTile b(A.rows);
-    if (b.tile >= A.ntile) return;
+    const StressTile<NEAR> b(A.rows);
+    if (NEAR && b.tile >= A.ntile) return;
     const int slab = b.tile / A.ntiles, tile = b.tile % A.ntiles;
     const int col = tile * TC + c;
     const bool act = col < A.ncols;

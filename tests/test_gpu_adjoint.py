@@ -268,3 +268,28 @@ def test_set_box_then_semi_implicit_step(bc):
     assert torch.equal(a, c) and torch.equal(b, d)
     ctx.close()
     ref.close()
+
+
+@pytest.mark.parametrize("prec,n,bc", [(B.PFT_C128, (64, 96, 96), (0, 0, 0)), (B.PFT_C128, (64, 96, 96), (0, 1, 2)),
+                                       (B.PFT_C64, (96, 96, 128), (0, 0, 0)), (B.PFT_C64, (96, 96, 128), (0, 2, 1))])
+def test_box_stress_of_a_doubled_cell(prec, n, bc):
+    """Fields repeated along x double H: dH/dLx stays, dH/dLy and dH/dLz double.
+    The cell's arrays are below 12 MiB and the doubled ones above, where the stress
+    workgroups are numbered for the L2 of an XCD."""
+    print("stress of a doubled cell", prec, n, bc, flush=True)
+    C, L = 2.0, [0.1 * a for a in n]
+    g = torch.Generator(device="cuda").manual_seed(11)
+    w = [0.2 * torch.randn(n, dtype=torch.complex128, device="cuda", generator=g) for _ in range(2)]
+    dL = []
+    for k in (1, 2):
+        fields = [torch.cat([x] * k).contiguous() for x in w]
+        ctx = B.Context(B.Params(k * n[0], n[1], n[2], k * L[0], L[1], L[2], 4, 0.4, 14.0, C, prec, 0, B.PFT_DIBLOCK, 0.0, 0, bc))
+        grad = [torch.empty_like(fields[0]) for _ in range(2)]
+        d = torch.empty(3, dtype=torch.complex128, device="cuda")
+        ctx.pft_adjoint(*fields, *grad, d)
+        dL.append(d.cpu().numpy())
+        ctx.close()
+    tol = 1e-10 if prec == B.PFT_C128 else 2e-5
+    for a in range(3):
+        want = dL[0][a] * (1 if a == 0 else 2)
+        assert abs(dL[1][a] - want) <= tol * (abs(want) + C * 2 * L[0] * L[1] * L[2] / (L[a] * (2 if a == 0 else 1))), a
