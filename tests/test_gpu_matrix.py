@@ -150,3 +150,42 @@ def test_passes_of_large_grids(n, bc, prec, scheme, axis, lines):
     ctx.close()
     assert torch.equal(got, ref) == lines
     assert (got - ref).abs().max() <= (1e-12 if prec == B.PFT_C128 else 2e-5) * ref.abs().max()
+
+
+def launches(ctx, wp, wm):
+    ctx.pft_profile_begin()
+    ctx.pft_propagate(wp, wm)
+    k = ctx.pft_profile_end()
+    return tuple(k[name][1] for name in ("yzpass", "zpass", "ypass", "xpass"))
+
+
+# (grid, walls, precision, yz or axis passes, shared by both sweeps): square planes, planes of one
+# launch, planes too long for one, and the sizes next to the limits of either
+SHARED = [((16, 32, 32), (0, 0, 0), 0, "yz", True), ((64, 64, 64), (0, 0, 0), 1, "yz", True), ((64, 64, 64), (0, 0, 0), 0, "yz", False),
+          ((8, 40, 24), (0, 0, 0), 0, "yz", True), ((8, 40, 48), (0, 2, 1), 1, "yz", True), ((8, 32, 32), (0, 1, 1), 0, "yz", True),
+          ((20, 48, 40), (1, 0, 0), 1, "yz", True), ((8, 48, 48), (0, 0, 1), 0, "axis", True), ((8, 64, 80), (0, 1, 0), 0, "axis", True),
+          ((8, 80, 96), (0, 0, 0), 1, "axis", True), ((8, 96, 80), (0, 0, 0), 0, "axis", False), ((80, 80, 64), (0, 0, 0), 1, "axis", True),
+          ((96, 96, 64), (0, 0, 0), 1, "axis", False)]
+
+
+@pytest.mark.parametrize("n,bc,prec,kind,shared", SHARED, ids=[f"{n}-{bc}-{'c64' if p else 'c128'}" for n, bc, p, _, _ in SHARED])
+def test_which_launches_run(n, bc, prec, kind, shared):
+    """The passes of one propagation by name and number: one launch for both sweeps
+    where they share it, twice as many with the sweeps one after the other, and no
+    yz pass once an axis of an uneven plane is a line transform."""
+    print("launches", n, bc, prec, flush=True)
+    wp, wm = (torch.zeros(n, dtype=torch.complex128, device=DEV) for _ in range(2))
+    ctx = B.Context(B.Params(*n, *[0.1 * a for a in n], 6, 0.4, 15.0, 2.0, prec, 0, B.PFT_DIBLOCK, 0.0, 0, bc))
+    K = ctx.K
+
+    def passes(kind, sweeps):
+        return (sweeps * (K + 1), 0, 0, sweeps * K) if kind == "yz" else (0, sweeps * (K + 1), sweeps * 2 * K, sweeps * K)
+
+    assert launches(ctx, wp, wm) == passes(kind, 1 if shared else 2)
+    ctx.pft_set_concurrent_sweeps(False)
+    assert launches(ctx, wp, wm) == passes(kind, 2)
+    ctx.pft_set_concurrent_sweeps(True)
+    ctx.pft_set_variant(1, 0)  # y by line transforms: nothing shared but a square plane's own pass
+    assert launches(ctx, wp, wm) == passes("yz" if kind == "yz" and n[1] == n[2] and not any(bc) else "axis",
+                                           1 if shared and n[1] == n[2] and not any(bc) else 2)
+    ctx.close()
