@@ -506,9 +506,13 @@ constexpr int kFusedMaxSpillWalls = 128;
 // Both sweeps share each launch while one array of the grid is smaller than
 // this, where launches and latency count: the launches of two streams and their
 // gaps cost more than one stream's passes leave idle (us per contour step, two
-// streams against shared launches: 32^3 complex float 14.3 / 12.0, 64 x 48 x 80
-// 46.4 / 40.1, complex double 53.4 / 50.9; at 64^3 complex double, 4 MiB, 32.1 /
-// 35.5).
+// streams against shared launches: 32^3 complex float 14.3 / 12.0, complex double
+// 15.8 / 13.8, 48^3 21.7 / 19.2 and 25.8 / 25.4, 64 x 48 x 80 46.4 / 40.1 and 53.4 / 50.9).
+// Complex double loses from 4 MiB on (64^3 32.1 / 35.5, 80 x 64 x 80 61.2 / 67.9, 96 x 80 x
+// 96 96.0 / 95.8).  Complex float still gains on uneven grids somewhat above (80 x 64 x 80,
+// 3.1 MiB, 59.3 / 52.7; 96 x 80 x 96, 5.6 MiB, 70.2 / 66.2) and is even on fused ones (80 x 64
+// x 64 32.8 / 32.6, 128 x 64 x 64 33.5 / 33.5): the limit is the one below which nothing
+// measured loses.
 constexpr int64_t kTogetherBytes = 4 << 20;
 
 // Walls along y or z have a fused pass in complex float only.
@@ -655,11 +659,10 @@ pft_status create_ctx(const pft_params* params, void* hip_stream, bool dual, pft
     for (int ax = 0; ax < 3; ++ax) {
         const int na = ax == 0 ? p.nx : ax == 1 ? p.ny : p.nz;
         const bool wall = p.bc[ax] != 0;
-        c->m[ax] = ax < 2 ? (dbl ? pft::mx_supported<double>(na, wall) : pft::mx_supported<float>(na, wall))
-                          : (dbl ? pft::mz_supported<double>(na, wall) : pft::mz_supported<float>(na, wall));
+        c->m[ax] = dbl ? pft::mline_supported<double>(na, wall) : pft::mline_supported<float>(na, wall);
     }
     c->pair = c->together && !c->mplane && pft::pair_supported(p.ny, p.nz);
-    // Long periodic z lines lose to the line transforms (z pass, us: complex float
+    // Long periodic z lines lose to the line transforms (z pass alone, us: complex float
     // 48 points 10.0 / 7.2, 80 points 14.1 / 13.8; complex double 64 points 11.2 /
     // 12.3, 80 points 17.2 / 17.2; between walls 80 points 15.7 / 19.6 and 16.0 /
     // 25.1), unless that lets a small grid share its launches.

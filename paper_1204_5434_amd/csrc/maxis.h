@@ -34,19 +34,32 @@ struct MXArgs {
     cx<T>* capV;
 };
 
+// Wavefronts of a workgroup.  They share the tables, and a grid has as many
+// workgroups as strips allow: two are quicker on few columns and slower on many,
+// eight are slower on both (x pass of 48 points in complex float, us with 2 / 4 / 8:
+// 1024 columns 5.4 / 5.9 / 8.5, 12288 columns 8.4 / 7.0 / 9.6; z pass of 64 points in
+// complex double 7.4 / 8.7 / 11.6 and 16.5 / 17.3 / 14.4).
 constexpr int kMXWaves = 4;
 
 template <typename T, int N, bool WALL>
 struct MXShape {
     static constexpr int kFrag = MSplit<N, WALL>::kFrag;
     static constexpr int kFragBytes = kFrag * (int)sizeof(T);
+    // Tables of 4 KB and more go through LDS (us, read from the caches / staged, 4096
+    // columns: z pass of 40 points in complex float 7.9 / 7.2, 80 points 18.5 / 14.3,
+    // complex double 40 points 8.9 / 7.5, 80 points 18.1 / 13.6); of smaller ones some lose
+    // and some gain (z pass of 24 points in complex double 4.7 / 4.9, in complex float 4.8 /
+    // 4.6, of 48 points 10.2 / 8.8).
     static constexpr bool kStage = kFragBytes >= 4096;
     static constexpr int kLdsBytes = kStage ? 2 * kFragBytes : 16;
-    // registers of a strip; long lines are compiled for two waves per SIMD
-    // (all 512 registers otherwise), and from 64 on an x pass loads U late
+    // registers of a strip; long lines are compiled for two waves per SIMD (all 512
+    // registers otherwise: 80 points in complex double, 12288 columns, us with the bound
+    // / without: x 21.3 / 25.9, z 24.3 / 32.1; 96 points in complex float 14.1 / 14.5 and
+    // 18.1 / 18.3; up to 64 points the bound changes 5% at most, either way)
     static constexpr int kStripRegs = MStrip<T, N>::NC * (N / 4) * (int)sizeof(T) / 4;
     static constexpr int kMinWaves = kStripRegs >= 40 ? 2 : 1;
-    static constexpr bool kEarly = kStripRegs < 64;
+    // every strip of a pass is loaded before its first product
+    static_assert(kStripRegs < 64, "three strips must fit the registers");
 };
 
 // A table on its way to slot 0 or 1 of LDS: requested before the strip's own
@@ -94,7 +107,7 @@ __device__ __forceinline__ void mx_body(const MXArgs<T>& A, unsigned bid, unsign
     }
     if (A.V) L.load(v, A.V + at, A.stride, act);
     if (A.E) L.load(e, A.E + at, A.stride, act);
-    if (S::kEarly && A.U) L.load(u, A.U + at, A.stride, act);
+    if (A.U) L.load(u, A.U + at, A.stride, act);
     const T *ff = A.ff, *fh = A.fh;
     if constexpr (S::kStage) {
         if (A.V) cf.commit(smem, 0);
@@ -111,7 +124,6 @@ __device__ __forceinline__ void mx_body(const MXArgs<T>& A, unsigned bid, unsign
         L.store(v, A.V + at, A.stride, act);
     }
     if (A.U) {
-        if (!S::kEarly) L.load(u, A.U + at, A.stride, act);
         mdiffuse<N, NC, WALL>(u.v, fh);
         if (A.capU) L.store(u, A.capU + at, A.stride, act);
         if (A.E) {
@@ -154,7 +166,6 @@ __device__ __forceinline__ void mz_body(const MArgs<T>& A, unsigned bid, unsigne
     const bool rqm4 = A.scheme == kSchemeRQM4;
     const T *ff = A.fzf_n, *fh = A.has_prev ? A.fzh_p : A.fzh_n;
     Strip q, e;
-    bool have_e = false;
     MTable<T, N, WALL> cf, ch;
     if constexpr (S::kStage) {
         if (rqm4) ch.fetch(fh);
@@ -170,17 +181,12 @@ __device__ __forceinline__ void mz_body(const MArgs<T>& A, unsigned bid, unsigne
     if (A.has_prev) {
         Strip v;
         L.load_line(q, (rqm4 ? A.U : A.V) + at, act);
-        if (S::kEarly) {
-            if (rqm4) L.load_line(v, A.V + at, act);
-            L.load_line(e, A.Ep + at, act);
-        }
-        have_e = true;
+        if (rqm4) L.load_line(v, A.V + at, act);
+        L.load_line(e, A.Ep + at, act);
         tables_ready();
         if (rqm4) mdiffuse<N, NC, WALL>(q.v, S::kStage ? reinterpret_cast<const T*>(smem + S::kFragBytes) : fh);
         if (A.hcap) L.store_line(q, A.hcap + at, act);
-        if (!S::kEarly) L.load_line(e, A.Ep + at, act);
         L.mul(q, e);
-        if (!S::kEarly && rqm4) L.load_line(v, A.V + at, act);
         if (rqm4)
             L.combine(q, v);
         else
@@ -207,7 +213,7 @@ __device__ __forceinline__ void mz_body(const MArgs<T>& A, unsigned bid, unsigne
         ff = reinterpret_cast<const T*>(smem);
         fh = reinterpret_cast<const T*>(smem + S::kFragBytes);
     }
-    if (!(have_e && A.En == A.Ep)) L.load_line(e, A.En + at, act);
+    if (!(A.has_prev && A.En == A.Ep)) L.load_line(e, A.En + at, act);
     L.mul(q, e);
     Strip w = q;
     L.mul(w, e);
@@ -237,18 +243,14 @@ __global__ __launch_bounds__(64 * kMXWaves, (MXShape<T, N, WALL>::kMinWaves)) vo
     mz_body<T, N, WALL>(A, blockIdx.x, smem);
 }
 
-// Line lengths with kernels: strided passes, z passes, and both between walls.
-#define PFT_MX_F32(X) X(8) X(12) X(16) X(20) X(24) X(32) X(40) X(48) X(64) X(80) X(96)
-#define PFT_MX_F64(X) X(8) X(12) X(16) X(20) X(24) X(32) X(40) X(48) X(64) X(80)
-#define PFT_MZ_F32(X) X(8) X(12) X(16) X(20) X(24) X(32) X(40) X(48) X(64) X(80) X(96)
-#define PFT_MZ_F64(X) X(8) X(12) X(16) X(20) X(24) X(32) X(40) X(48) X(64) X(80)
-#define PFT_MWALL_F32(X) X(8) X(12) X(16) X(20) X(24) X(32) X(40) X(48) X(64) X(80)
-#define PFT_MWALL_F64(X) X(8) X(12) X(16) X(20) X(24) X(32) X(40) X(48) X(64) X(80)
+// Line lengths with kernels: periodic, and between walls.
+#define PFT_MLINE_F32(X) X(8) X(12) X(16) X(20) X(24) X(32) X(40) X(48) X(64) X(80) X(96)
+#define PFT_MLINE_F64(X) X(8) X(12) X(16) X(20) X(24) X(32) X(40) X(48) X(64) X(80)
+#define PFT_MWALL(X) X(8) X(12) X(16) X(20) X(24) X(32) X(40) X(48) X(64) X(80)
 
+// The lengths are the same for strided and z passes.
 template <typename T>
-bool mx_supported(int n, bool wall);
-template <typename T>
-bool mz_supported(int n, bool wall);
+bool mline_supported(int n, bool wall);
 
 // nsweeps 1 (a0) or 2: both sweeps' passes in one launch.
 template <typename T>

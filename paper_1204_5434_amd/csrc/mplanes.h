@@ -26,20 +26,16 @@ struct MShape {
     static constexpr int kStrips = PW * N / CPS;
     static constexpr int kThreads = 64 * kStrips;
     static constexpr int RP = N + 1;  // odd pitch: strips of rows and of columns both spread over the banks
-    // complex double at 128: the plane exceeds LDS, real and imaginary parts go through it one after the other
-    static constexpr bool kHalves = (int64_t)PW * N * RP * (int64_t)sizeof(cx<T>) > 160 * 1024;
-    static constexpr int kPlaneBytes = PW * N * RP * (int)sizeof(T) * (kHalves ? 1 : 2);
-    // Matrix tables in LDS: all four of a pass where they fit beside the plane,
-    // one at a time where that fits, else read from global memory.
-    static constexpr int kFragBytes = MSplit<N>::kFrag * (int)sizeof(T);
+    // In LDS: the plane, then the four matrix tables of a pass.
+    static constexpr int kPlaneBytes = PW * N * RP * (int)sizeof(cx<T>);
     static constexpr int kPlanePad = (kPlaneBytes + 15) / 16 * 16;
-    static constexpr int kSlots = kPlanePad + 4 * kFragBytes <= 160 * 1024 ? 4 : kPlanePad + kFragBytes <= 160 * 1024 ? 1 : 0;
-    static constexpr int kLdsBytes = kPlanePad + kSlots * kFragBytes;
-    // registers of a strip, and what a lane may use at this workgroup size
+    static constexpr int kFragBytes = MSplit<N>::kFrag * (int)sizeof(T);
+    static constexpr int kLdsBytes = kPlanePad + 4 * kFragBytes;
+    static_assert(kLdsBytes <= 160 * 1024, "the plane and its tables must fit in LDS");
+    // V and E are loaded before U's transforms: three strips, and the accumulators of
+    // a product, in the registers of a lane at this workgroup size.
     static constexpr int kStripRegs = NC * (N / 4) * (int)sizeof(T) / 4;
-    static constexpr int kRegs = 512 / ((kStrips + 3) / 4);
-    // V and E are loaded before U's transforms where three strips fit the registers
-    static constexpr bool kEarly = 4 * kStripRegs + 64 <= kRegs;
+    static_assert(4 * kStripRegs + 64 <= 512 / ((kStrips + 3) / 4), "three strips must fit the registers");
 };
 
 template <typename T, int N>
@@ -57,9 +53,8 @@ __device__ __forceinline__ void myz_body(const MArgs<T>& A, unsigned bid, unsign
     const int64_t oc = pbase + col, orow = pbase + (int64_t)col * N;
     T* sh = reinterpret_cast<T*>(smem);
 
-    // Matrix tables: slot 0 (1, 2, 3) of LDS holds the y and z tables for h/2
-    // and the z and y tables for h; with one slot each is brought in when the
-    // plane turns, or by itself.
+    // Matrix tables: slots 0 and 1 of LDS hold the y and z tables for h/2, slots 2
+    // and 3 the z and y tables for h.
     T* const fs = reinterpret_cast<T*>(smem + S::kPlanePad);
     constexpr int kFrag = MSplit<N>::kFrag;
     using Quad = float __attribute__((ext_vector_type(4)));
@@ -80,35 +75,15 @@ __device__ __forceinline__ void myz_body(const MArgs<T>& A, unsigned bid, unsign
             if (i < kQuads) reinterpret_cast<Quad*>(fs + slot * kFrag)[i] = c.r[decltype(I)::value];
         });
     };
-    auto bring = [&](const T* f, int slot) {
-        Copy c;
-        fetch(c, f);
-        __syncthreads();
-        commit(c, slot);
-        __syncthreads();
-    };
-    auto diff = [&](Strip& x, const T* f, int slot) {
-        if constexpr (S::kSlots == 0)
-            mdiffuse<N, NC>(x.v, f);
-        else
-            mdiffuse<N, NC>(x.v, static_cast<const T*>(fs + (S::kSlots == 4 ? slot : 0) * kFrag));
-    };
-    // turn a strip of columns into a strip of rows, and back; f: the table that
-    // the next diffusion reads (one slot)
-    auto turn = [&](Strip& x, bool to_rows, const T* f) {
-        Copy c;
-        if constexpr (S::kSlots == 1) {
-            if (f) fetch(c, f);
-        }
+    auto diff = [&](Strip& x, int slot) { mdiffuse<N, NC>(x.v, static_cast<const T*>(fs + slot * kFrag)); };
+    // turn a strip of columns into a strip of rows, and back
+    auto turn = [&](Strip& x, bool to_rows) {
         const int wbase = pw * N * RP + (to_rows ? col : col * RP), ws = to_rows ? RP : 1;
         const int rbase = pw * N * RP + (to_rows ? col * RP : col), rs = to_rows ? 1 : RP;
         constexpr int R = MSplit<N>::R;
+        __syncthreads();
         if constexpr (NC == 2) {
             cx<T>* s2 = reinterpret_cast<cx<T>*>(sh);
-            __syncthreads();
-            if constexpr (S::kSlots == 1) {
-                if (f) commit(c, 0);
-            }
             L.each([&](auto TI, auto I, int pt) {
                 constexpr int k = decltype(TI)::value * R + decltype(I)::value;
                 s2[wbase + pt * ws] = cx<T>{x.v[0][k], x.v[1][k]};
@@ -120,11 +95,7 @@ __device__ __forceinline__ void myz_body(const MArgs<T>& A, unsigned bid, unsign
                 x.v[0][k] = a.re;
                 x.v[1][k] = a.im;
             });
-        } else if constexpr (!S::kHalves) {
-            __syncthreads();
-            if constexpr (S::kSlots == 1) {
-                if (f) commit(c, 0);
-            }
+        } else {
             L.each([&](auto TI, auto I, int pt) {
                 sh[2 * (wbase + pt * ws) + L.comp] = x.v[0][decltype(TI)::value * R + decltype(I)::value];
             });
@@ -132,27 +103,10 @@ __device__ __forceinline__ void myz_body(const MArgs<T>& A, unsigned bid, unsign
             L.each([&](auto TI, auto I, int pt) {
                 x.v[0][decltype(TI)::value * R + decltype(I)::value] = sh[2 * (rbase + pt * rs) + L.comp];
             });
-        } else {
-            for (int half = 0; half < 2; ++half) {
-                __syncthreads();
-                if constexpr (S::kSlots == 1) {
-                    if (f && half == 0) commit(c, 0);
-                }
-                if (L.comp == half)
-                    L.each([&](auto TI, auto I, int pt) {
-                        sh[wbase + pt * ws] = x.v[0][decltype(TI)::value * R + decltype(I)::value];
-                    });
-                __syncthreads();
-                if (L.comp == half)
-                    L.each([&](auto TI, auto I, int pt) {
-                        x.v[0][decltype(TI)::value * R + decltype(I)::value] = sh[rbase + pt * rs];
-                    });
-            }
         }
     };
 
     Strip q, e;
-    bool have_e = false;
     const bool rqm4 = A.scheme == kSchemeRQM4;
     // The tables are requested before the plane, so that they wait for nothing
     // else (memory answers a wavefront in order).
@@ -160,53 +114,39 @@ __device__ __forceinline__ void myz_body(const MArgs<T>& A, unsigned bid, unsign
     const T* const fzh = A.has_prev ? A.fzh_p : A.fzh_n;
     Copy c0, c1, c2, c3;
     if (rqm4) {
-        if constexpr (S::kSlots == 4) {
-            fetch(c0, fyh);
-            fetch(c1, fzh);
-        } else if constexpr (S::kSlots == 1) {
-            fetch(c0, A.has_prev ? fyh : fzh);
-        }
+        fetch(c0, fyh);
+        fetch(c1, fzh);
     }
-    if constexpr (S::kSlots == 4) {
-        if (A.has_next) {
-            fetch(c2, A.fzf_n);
-            fetch(c3, A.fyf_n);
-        }
+    if (A.has_next) {
+        fetch(c2, A.fzf_n);
+        fetch(c3, A.fyf_n);
     }
     auto tables_ready = [&]() {
-        if constexpr (S::kSlots > 0) {
-            if (rqm4) commit(c0, 0);
-            if constexpr (S::kSlots == 4) {
-                if (rqm4) commit(c1, 1);
-                if (A.has_next) {
-                    commit(c2, 2);
-                    commit(c3, 3);
-                }
-            }
-            __syncthreads();
+        if (rqm4) {
+            commit(c0, 0);
+            commit(c1, 1);
         }
+        if (A.has_next) {
+            commit(c2, 2);
+            commit(c3, 3);
+        }
+        __syncthreads();
     };
     if (A.has_prev && rqm4) {
         L.load(q, A.U + oc, N, act);
         Strip v;
-        if constexpr (S::kEarly) {
-            L.load_line(v, A.V + orow, act);
-            L.load_line(e, A.Ep + orow, act);
-        }
+        L.load_line(v, A.V + orow, act);
+        L.load_line(e, A.Ep + orow, act);
         tables_ready();
-        diff(q, fyh, 0);
-        turn(q, true, fzh);
-        diff(q, fzh, 1);
+        diff(q, 0);
+        turn(q, true);
+        diff(q, 1);
         if (A.hcap) L.store_line(q, A.hcap + orow, act);
-        if constexpr (!S::kEarly) L.load_line(e, A.Ep + orow, act);
-        have_e = true;
         L.mul(q, e);
-        if constexpr (!S::kEarly) L.load_line(v, A.V + orow, act);
         L.combine(q, v);
     } else if (A.has_prev) {
         L.load_line(q, A.V + orow, act);
         L.load_line(e, A.Ep + orow, act);
-        have_e = true;
         tables_ready();
         if (A.hcap) L.store_line(q, A.hcap + orow, act);
         L.mul(q, e);
@@ -216,44 +156,34 @@ __device__ __forceinline__ void myz_body(const MArgs<T>& A, unsigned bid, unsign
             L.load_line(q, A.qin + orow, act);
         else
             L.one(q);
-        if (A.has_next) {
-            L.load_line(e, A.En + orow, act);
-            have_e = true;
-        }
+        if (A.has_next) L.load_line(e, A.En + orow, act);
         tables_ready();
     }
     if (A.qout) L.store_line(q, A.qout + orow, act);
     if (!A.has_next) return;
 
     if (A.has_prev && A.En != A.Ep) L.load_line(e, A.En + orow, act);
-    if (rqm4 && A.has_prev) {
-        // tables of a next step of another length (one slot: its first table)
-        if constexpr (S::kSlots == 4) {
-            if (A.fyh_n != fyh || A.fzh_n != fzh) {
-                fetch(c0, A.fyh_n);
-                fetch(c1, A.fzh_n);
-                __syncthreads();
-                commit(c0, 0);
-                commit(c1, 1);
-                __syncthreads();
-            }
-        } else if constexpr (S::kSlots == 1) {
-            if (A.fzh_n != fzh) bring(A.fzh_n, 0);
-        }
+    if (rqm4 && A.has_prev && (A.fyh_n != fyh || A.fzh_n != fzh)) {
+        // the next step has another length
+        fetch(c0, A.fyh_n);
+        fetch(c1, A.fzh_n);
+        __syncthreads();
+        commit(c0, 0);
+        commit(c1, 1);
+        __syncthreads();
     }
     L.mul(q, e);
     Strip w = q;
     L.mul(w, e);
     if (rqm4) {
-        diff(q, A.fzh_n, 1);
-        turn(q, false, A.fyh_n);
-        diff(q, A.fyh_n, 0);
+        diff(q, 1);
+        turn(q, false);
+        diff(q, 0);
         L.store(q, A.U + oc, N, act);
     }
-    if constexpr (S::kSlots == 1) bring(A.fzf_n, 0);
-    diff(w, A.fzf_n, 2);
-    turn(w, false, A.fyf_n);
-    diff(w, A.fyf_n, 3);
+    diff(w, 2);
+    turn(w, false);
+    diff(w, 3);
     L.store(w, A.V + oc, N, act);
 }
 
@@ -277,8 +207,7 @@ __global__ __launch_bounds__((MShape<T, N>::kThreads)) void k_myz_batch(const MA
 }
 
 // Plane sides (= ny = nz) of the yz pass.
-#define PFT_MPLANE_F32(X) X(8) X(12) X(16) X(20) X(24) X(32) X(40) X(48) X(64)
-#define PFT_MPLANE_F64(X) X(8) X(12) X(16) X(20) X(24) X(32) X(40) X(48) X(64)
+#define PFT_MPLANE(X) X(8) X(12) X(16) X(20) X(24) X(32) X(40) X(48) X(64)
 
 template <typename T>
 bool mplane_supported(int n);
