@@ -166,6 +166,7 @@ __device__ __forceinline__ void mz_body(const MArgs<T>& A, unsigned bid, unsigne
     const bool rqm4 = A.scheme == kSchemeRQM4;
     const T *ff = A.fzf_n, *fh = A.has_prev ? A.fzh_p : A.fzh_n;
     Strip q, e;
+    bool have_e = false;  // has_prev, where the compiler sees it: tested itself, it costs 8 to 20 registers
     MTable<T, N, WALL> cf, ch;
     if constexpr (S::kStage) {
         if (rqm4) ch.fetch(fh);
@@ -183,6 +184,7 @@ __device__ __forceinline__ void mz_body(const MArgs<T>& A, unsigned bid, unsigne
         L.load_line(q, (rqm4 ? A.U : A.V) + at, act);
         if (rqm4) L.load_line(v, A.V + at, act);
         L.load_line(e, A.Ep + at, act);
+        have_e = true;
         tables_ready();
         if (rqm4) mdiffuse<N, NC, WALL>(q.v, S::kStage ? reinterpret_cast<const T*>(smem + S::kFragBytes) : fh);
         if (A.hcap) L.store_line(q, A.hcap + at, act);
@@ -213,7 +215,7 @@ __device__ __forceinline__ void mz_body(const MArgs<T>& A, unsigned bid, unsigne
         ff = reinterpret_cast<const T*>(smem);
         fh = reinterpret_cast<const T*>(smem + S::kFragBytes);
     }
-    if (!(A.has_prev && A.En == A.Ep)) L.load_line(e, A.En + at, act);
+    if (!(have_e && A.En == A.Ep)) L.load_line(e, A.En + at, act);
     L.mul(q, e);
     Strip w = q;
     L.mul(w, e);
