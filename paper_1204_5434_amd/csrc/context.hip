@@ -546,8 +546,8 @@ static bool fused_default(const pft_params& p)
 // 49.8, 80 x 80 alike; complex double 80 x 80, two sweeps 32 planes 56.6 / 51.6, 64
 // planes 64.0 / 61.6, 96 planes 81.3 / 87.2, one 52.6 / 40.2, 58.4 / 52.2, 67.2 / 64.4
 // and with 128 planes 66.5 / 68.5.  The plain split step, whose fused pass makes up
-// less of a step: complex float 128 x 128, two sweeps 40 planes 30.7 / 30.4, 48 planes
-// 30.3 / 31.4, 64 planes 34.0 / 37.0, one 128 planes 33.6 / 32.5, 192 planes 39.5 / 41.5;
+// less of a step: complex float 128 x 128, two sweeps 40 planes 30.4 / 30.2, 48 planes
+// 31.3 / 29.2, 64 planes 33.5 / 34.8, one 128 planes 33.6 / 32.4, 192 planes 40.0 / 41.5;
 // 96 x 96, two sweeps 24 planes 23.3 / 22.2, 32 planes 24.1 / 24.5, one 20.4 / 20.4 and
 // 21.2 / 21.3; 80 x 80, two sweeps 16 planes 17.9 / 18.5, one 15.6 / 16.8; complex
 // double 80 x 80, two sweeps 48 planes 30.8 / 28.7, 64 planes 31.6 / 32.1, one 96 planes
@@ -559,7 +559,7 @@ static bool few_planes(const pft_params& p, int sweeps)
     if (p.bc[1] || p.bc[2]) return false;
     if (p.scheme == PFT_SPLIT2) {
         if (p.precision == PFT_C128) return p.nx <= (sweeps == 2 ? 48 : 96);
-        return p.ny >= 128 ? p.nx <= (sweeps == 2 ? 40 : 128) : p.ny == 96 && p.nx <= 24;
+        return p.ny >= 128 ? p.nx <= (sweeps == 2 ? 48 : 128) : p.ny == 96 && p.nx <= 24;
     }
     if (p.precision == PFT_C128) return p.nx * sweeps <= (sweeps == 2 ? 128 : 96);
     return p.ny >= 128 ? p.nx * sweeps <= 128 : p.nx <= 32;
@@ -596,8 +596,9 @@ static int untuned_x_variant(const pft_params& p, bool fused)
 // 64.6, 87.8 / 87.9; 80 points 72.3 / 72.1, 78.5 / 77.1, 111.6 / 107.2; 96 points 78.6 / 79.8,
 // 89.1 / 88.8, 123.5 / 123.1.  x, 48 points 55.7 / 57.1, 57.3 / 52.8, 75.8 / 73.1; 64
 // points alike, 80 points 75.2 / 75.3, 96 points 80.7 / 81.9; the plain split step alike.
-// At 40 points 52.9 / 57.5 and 69.5 / 72.6.  Between walls alike at 48 and 64 points, at
-// 80 points x 77.3 / 79.7, y 82.1 / 83.3.
+// At 40 points 52.9 / 57.5 and 69.5 / 72.6.  Beside long z lines y passes of 64 points
+// and more stay: 128 x 256 columns, 64 points 105.5 / 109.5, 96 points 147.0 / 149.7.
+// Between walls alike at 48 and 64 points, at 80 points x 77.3 / 79.7, y 82.1 / 83.3.
 // Complex float, z between walls: 80 points 77.6 / 76.4 at 96 x 128 columns, 118.7 / 114.7 at
 // 192 x 128; 64 points 72.0 / 74.4 and 104.7 / 101.9, in the plain split step 39.7 / 38.4 and
 // 52.3 / 47.9.
@@ -613,6 +614,7 @@ static bool lines_faster(const pft_params& p, int ax)
     if (p.precision == PFT_C128)
         return ax == 2 && !wall && (n[2] == 48 || (n[2] == 64 && (split2 || cols > 16384)));
     if (ax == 2) return wall && (n[2] == 80 || (n[2] == 64 && split2));
+    if (ax == 1 && n[1] >= 64 && p.nz > 128) return false;
     return cols >= 16384 && n[ax] >= 48 && n[ax] <= (ax == 1 && !wall ? 96 : 64);
 }
 

@@ -29,7 +29,7 @@ def test_schedule_by_number_of_planes(prec, side, model, few, enough):
 
 
 # the plain split step's lines: (precision, side, model, largest count on the axis schedule, next count)
-SPLIT2 = [(B.PFT_C64, 128, 0, 40, 48), (B.PFT_C64, 128, 1, 128, 192), (B.PFT_C64, 96, 0, 24, 32), (B.PFT_C64, 96, 1, 24, 32),
+SPLIT2 = [(B.PFT_C64, 128, 0, 48, 64), (B.PFT_C64, 128, 1, 128, 192), (B.PFT_C64, 96, 0, 24, 32), (B.PFT_C64, 96, 1, 24, 32),
           (B.PFT_C64, 80, 0, None, 8), (B.PFT_C64, 80, 1, None, 8), (B.PFT_C128, 80, 0, 48, 64), (B.PFT_C128, 80, 1, 96, 128)]
 
 

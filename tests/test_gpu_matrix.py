@@ -127,7 +127,7 @@ def test_constant_and_nonfinite_fields(prec):
 # which passes of large grids run by line transforms, on both sides of each line:
 # (grid, walls, precision, scheme, axis, by lines)
 LINES = [((128, 48, 128), (0, 0, 0), 1, 0, 1, True), ((96, 48, 128), (0, 0, 0), 1, 0, 1, False),
-         ((128, 40, 128), (0, 0, 0), 1, 0, 1, False), ((128, 96, 128), (0, 0, 0), 1, 1, 1, True),
+         ((128, 40, 128), (0, 0, 0), 1, 0, 1, False), ((96, 64, 192), (0, 0, 0), 1, 0, 1, False), ((128, 96, 128), (0, 0, 0), 1, 1, 1, True),
          ((64, 128, 128), (0, 0, 0), 1, 0, 0, True), ((80, 192, 128), (0, 0, 0), 1, 0, 0, False),
          ((128, 64, 128), (0, 2, 0), 1, 0, 1, True), ((128, 80, 128), (0, 1, 0), 1, 0, 1, False),
          ((96, 96, 80), (0, 0, 1), 1, 0, 2, True), ((96, 96, 64), (0, 0, 2), 1, 0, 2, False), ((96, 96, 64), (0, 0, 2), 1, 1, 2, True),
