@@ -34,8 +34,13 @@ GRIDS = [((80, 96, 40), (P, P, R)), ((24, 192, 96), (P, P, P)), ((96, 20, 192), 
          ((16, 32, 32), (P, P, P)), ((12, 64, 64), (P, P, P)), ((20, 48, 48), (P, P, P)), ((48, 24, 40), (P, P, P)),
          ((16, 24, 40), (R, R, P)), ((12, 20, 48), (P, R, R)), ((24, 80, 64), (P, R, R)), ((16, 48, 20), (P, A, P)),
          ((20, 24, 40), (A, P, R)), ((16, 64, 80), (P, A, A))]
-CASES = [(n, bc, scheme, prec) for n, bc in GRIDS for scheme in (B.PFT_SPLIT2, B.PFT_RQM4)
+CASES = [(n, bc, scheme, prec, 20, 0.12) for n, bc in GRIDS for scheme in (B.PFT_SPLIT2, B.PFT_RQM4)
          for prec in (B.PFT_C128, B.PFT_C64) if A not in bc or prec == B.PFT_C64]
+# a step and spacing at which matrix products that added up to the mean of q, instead of
+# to its variation, would lose their smallest entries: 0.45 u a step for each axis of 64 points
+CASES += [(n, bc, B.PFT_RQM4, B.PFT_C64, 50, 6 / 64) for n, bc in [
+    ((64, 64, 64), (P, P, P)), ((16, 64, 64), (P, P, P)), ((64, 16, 12), (P, P, P)), ((16, 64, 12), (P, P, P)),
+    ((16, 12, 64), (P, P, P)), ((64, 64, 80), (P, P, R)), ((16, 64, 12), (P, A, P)), ((12, 16, 64), (P, P, A))]]
 
 
 def axis_sums(n, L, h, wall):
@@ -52,11 +57,11 @@ def axis_sums(n, L, h, wall):
     return out
 
 
-@pytest.mark.parametrize("n,bc,scheme,prec", CASES, ids=[
-    f"{n}-{bc}-{'split2' if s else 'rqm4'}-{'c64' if p else 'c128'}" for n, bc, s, p in CASES])
-def test_the_mean_does_not_drift(n, bc, scheme, prec):
-    print("mean of q", n, bc, scheme, prec, flush=True)
-    ns, L = 20, tuple(0.12 * a for a in n)
+@pytest.mark.parametrize("n,bc,scheme,prec,ns,dx", CASES, ids=[
+    f"{n}-{bc}-{'split2' if s else 'rqm4'}-{'c64' if p else 'c128'}-{ns}" for n, bc, s, p, ns, _ in CASES])
+def test_the_mean_does_not_drift(n, bc, scheme, prec, ns, dx):
+    print("mean of q", n, bc, scheme, prec, ns, flush=True)
+    L = tuple(dx * a for a in n)
     ctx = B.Context(B.Params(*n, *L, ns, 0.5, 15.0, 2.0, prec, scheme, B.PFT_DIBLOCK, 0.0, 0, bc))
     zero = torch.zeros(n, dtype=torch.complex128, device="cuda")
     ctx.pft_propagate(zero, zero)
