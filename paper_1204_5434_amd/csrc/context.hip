@@ -553,7 +553,7 @@ static bool fused_default(const pft_params& p)
 // double 80 x 80, two sweeps 48 planes 30.8 / 28.7, 64 planes 31.6 / 32.1, one 96 planes
 // 33.8 / 33.2, 128 planes 33.8 / 35.9.
 // A sweep that waits for its copies to the host (storage in host memory) keeps the
-// fused pass: 128^3 complex float, 148 / 157 ms per evaluation.
+// fused pass: 128^3 complex float, 104.6 / 108.2 ms per evaluation.
 static bool few_planes(const pft_params& p, int sweeps)
 {
     if (p.bc[1] || p.bc[2]) return false;

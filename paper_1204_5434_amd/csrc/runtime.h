@@ -546,8 +546,10 @@ pft_status step_body(pft_ctx* c, int j, const Work& w = Work(), cx<T>* capA = nu
 // the next reads it (us per contour step, both sweeps: 256^3 complex double 1879
 // whole, 1755 in slabs of 64 MiB, 1791 of 32, 1833 of 24, 2008 of 16, whose
 // launches no longer fill the device; complex float 894 / 861 / 882 / 893 / 927;
-// a smaller array gains nothing: 256 x 128 x 128 complex double, one of 64 MiB,
-// 415 whole, 427 in two).  A sweep that runs alone has the cache and the memory to
+// other shapes, us per evaluation of 6 steps: complex double 256 x 128 x 256, 128 MiB,
+// 6020 / 5710, 256 x 256 x 192 9390 / 9320, 192 x 256 x 256 with walled z 9200 / 9115; complex
+// float, 128 MiB at 256^3, 5940 / 5725.  A smaller array gains nothing: 256 x 128 x 128
+// complex double, one of 64 MiB, 415 whole, 427 in two).  A sweep that runs alone has the cache and the memory to
 // itself and gains nothing either (256^3, ms per evaluation of 6 steps, whole / slabs:
 // sweeps one after the other in complex double 12.87 / 12.93, in complex float 5.95 /
 // 6.00, q stored alone 14.37 / 14.50 and 7.51 / 7.61, Edwards model 6.80 / 6.80 and 3.16 /
